@@ -265,15 +265,6 @@ struct Chunk {
     }
 };
 
-// Queue a matrix build; a 7-qubit matrix is built by kBuildParts7 work-groups.
-void push_build(Chunk& c, BuildOp bo) {
-    const int parts = bo.k == 7 ? kBuildParts7 : 1;
-    for (int p = 0; p < parts; ++p) {
-        bo.part = p;
-        c.bops.push_back(bo);
-    }
-}
-
 hipError_t next_event(qsim_state_s* s, hipEvent_t* e) {
     if (s->pool_used == s->pool.size()) {
         hipEvent_t ne;
@@ -321,8 +312,10 @@ qsim_status flush(qsim_state_s* s, Chunk& c) {
         std::memset(&r, 0, sizeof(r));
         r.kind = 5;
         r.k = (int)c.bops.size();
+        int kmax = 1;
+        for (const BuildOp& bo : c.bops) kmax = std::max(kmax, (int)bo.k);
         HIP_TRY(rec_begin(s, r), "event record");
-        HIP_TRY(launch_build(reinterpret_cast<const BuildOp*>(dev + ob), (int)c.bops.size(),
+        HIP_TRY(launch_build(reinterpret_cast<const BuildOp*>(dev + ob), (int)c.bops.size(), kmax,
                              reinterpret_cast<const BuildGate*>(dev + gb),
                              reinterpret_cast<const double*>(dev + db), mats, s->st),
                 "matrix build launch");
@@ -423,7 +416,7 @@ qsim_status add_cluster(qsim_state_s* s, Chunk& c, int k, const int* qubits, con
                         bool fold_init = false) {
     size_t dense_need = 0;
     for (int gi : members) if (gates[gi].kind == G_DENSE) dense_need += size_t(2) << (2 * gates[gi].k);
-    const size_t need = align256((c.bops.size() + kBuildParts7) * sizeof(BuildOp)) +
+    const size_t need = align256((c.bops.size() + 1) * sizeof(BuildOp)) +
                         align256((c.bgates.size() + members.size() + epi_gates.size()) * sizeof(BuildGate)) +
                         align256((c.dense.size() + dense_need) * sizeof(double)) +
                         align256((c.epis.size() + 1) * sizeof(EpiDesc));
@@ -447,7 +440,7 @@ qsim_status add_cluster(qsim_state_s* s, Chunk& c, int k, const int* qubits, con
     EpiDesc e;
     if (qsim_status r = split_epilogue(pos_of, gates, epi_gates, c.bgates, c.dense, e)) return r;
     bo.n_gates = (int)c.bgates.size() - bo.gate0;
-    push_build(c, bo);
+    c.bops.push_back(bo);
     Chunk::Item it;
     std::memset(&it, 0, sizeof(it));
     it.kind = fold_init ? 6 : 0;
@@ -479,7 +472,7 @@ qsim_status add_fold2(qsim_state_s* s, Chunk& c, const SOp& A, const SOp& B, con
         for (int gi : op->members) if (gates[gi].kind == G_DENSE) dense_need += size_t(2) << (2 * gates[gi].k);
         ng += op->members.size() + op->epi.size();
     }
-    const size_t need = align256((c.bops.size() + 2 * kBuildParts7) * sizeof(BuildOp)) +
+    const size_t need = align256((c.bops.size() + 2) * sizeof(BuildOp)) +
                         align256((c.bgates.size() + ng) * sizeof(BuildGate)) +
                         align256((c.dense.size() + dense_need) * sizeof(double)) +
                         align256((c.epis.size() + 2) * sizeof(EpiDesc));
@@ -503,7 +496,7 @@ qsim_status add_fold2(qsim_state_s* s, Chunk& c, const SOp& A, const SOp& B, con
     ba.out_off = slotA * sb;
     for (int gi : A.members) c.bgates.push_back(to_build_gate(gates[gi], posA, c.dense));
     ba.n_gates = (int)c.bgates.size() - ba.gate0;
-    push_build(c, ba);
+    c.bops.push_back(ba);
     // B: A's epilogue terms on B's targets, B's gates, B's own epilogue terms on its targets
     BuildOp bb;
     std::memset(&bb, 0, sizeof(bb));
@@ -535,7 +528,7 @@ qsim_status add_fold2(qsim_state_s* s, Chunk& c, const SOp& A, const SOp& B, con
         bb.is_double = 1;
         bb.layout = LAYOUT_PLAIN;
     }
-    push_build(c, bb);
+    c.bops.push_back(bb);
     Chunk::Item it;
     std::memset(&it, 0, sizeof(it));
     it.kind = 8;
@@ -650,7 +643,7 @@ qsim_status add_pair(qsim_state_s* s, Chunk& c, const SOp& A, const SOp* Bp, con
         EpiDesc e;
         if (qsim_status r = split_epilogue(pos_of, gates, ops[m]->epi, c.bgates, c.dense, e)) return r;
         bo.n_gates = (int)c.bgates.size() - bo.gate0;
-        push_build(c, bo);
+        c.bops.push_back(bo);
         int epi = -1;
         if (e.n_cc || e.n_mix || e.n_ph) {
             epi = (int)c.epis.size();

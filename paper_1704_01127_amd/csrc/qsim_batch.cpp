@@ -483,7 +483,9 @@ qsim_status qsim_batch_run(qsim_batch b, void* dev_workspace, size_t ws_bytes, v
     put(b->off_bgates, b->bgates.data(), b->bgates.size() * sizeof(BuildGate));
     put(b->off_dense, b->dense.data(), b->dense.size() * sizeof(double));
     HIP_TRY(hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, st), "upload batch descriptors");
-    HIP_TRY(launch_build(reinterpret_cast<const BuildOp*>(ws + b->off_bops), (int)b->bops.size(),
+    int build_kmax = 1;
+    for (const BuildOp& bo : b->bops) build_kmax = std::max(build_kmax, (int)bo.k);
+    HIP_TRY(launch_build(reinterpret_cast<const BuildOp*>(ws + b->off_bops), (int)b->bops.size(), build_kmax,
                          reinterpret_cast<const BuildGate*>(ws + b->off_bgates),
                          reinterpret_cast<const double*>(ws + b->off_dense), ws + b->off_mats, st),
             "matrix build launch");

@@ -101,16 +101,13 @@ enum : int32_t {
     LAYOUT_SPLIT7 = 5     // k = 7 float: fp16 hi / lo halves of 16 x Re M and 16 x Im M
 };
 
-// A 7-qubit matrix is built by kBuildParts7 work-groups, each owning 32 of
-// its 128 columns (part p: columns 32 p .. 32 p + 31); smaller ones by one.
-constexpr int kBuildParts7 = 4;
 struct BuildOp {
     int32_t k;
     int32_t n_gates;
     int32_t gate0;      // first BuildGate of this op
     int32_t layout;
     int32_t is_double;  // element type of the output
-    int32_t part;       // k = 7: which quarter of the columns this work-group builds
+    int32_t pad;
     int64_t out_off;    // byte offset of the output inside the matrix region
 };
 
@@ -212,7 +209,8 @@ hipError_t launch_fold2(void* psi, const ClusterGeom& g2, const void* mat2, cons
 // and its diagonal epilogue, written in one pass.
 hipError_t launch_init_cluster(void* psi, bool dbl, const ClusterGeom& g, const void* mat, const EpiDesc* epi,
                                hipStream_t st);
-hipError_t launch_build(const BuildOp* ops, int n_ops, const BuildGate* gates, const double* dense,
+// Builds n_ops matrices of at most kmax qubits (device descriptors).
+hipError_t launch_build(const BuildOp* ops, int n_ops, int kmax, const BuildGate* gates, const double* dense,
                         char* mat_base, hipStream_t st);
 // Variant of the cluster kernel chosen for (dtype, k, n, targets).
 int cluster_layout(bool dbl, int k, int n);

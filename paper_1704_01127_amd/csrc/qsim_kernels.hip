@@ -3036,191 +3036,289 @@ __global__ __launch_bounds__(256) void k_init_cluster(typename Cplx<T>::type* __
 }
 
 // ------------------------------------------------------------ cluster-matrix builder
-// One work-group (64 threads) per cluster; a 7-qubit cluster takes
-// kBuildParts7 of them, each with 32 of its columns. Thread x owns column x of
-// the cluster matrix: it starts from the basis vector e_x of the 2^k space
-// and applies the cluster's gates in order, in float64 (the matrix is reused
-// for all 2^(n-k) columns of the state, Sec. 3.2, so building it is cheap).
-// The result is then written in the layout of the kernel that will apply it.
-// The columns are interleaved in LDS (real / imaginary part c of entry i of
-// local column x at (2 i + c) * cs + x, cs = the work-group's column count):
-// the threads touch consecutive words at every step (a column per contiguous
-// block put them a multiple of 256 words apart, all in one bank).
-// 4 waves per matrix (a quarter of a 7-qubit matrix): each column is worked
-// on by kBuildThreads / (columns held) threads, every gate split over them
+// A cluster's matrix is built column by column in float64: column x starts as
+// the basis vector e_x of the 2^k space and takes the cluster's gates in
+// order (it is reused for all 2^(n-k) columns of the state, Sec. 3.2). The
+// result is written in the layout of the kernel that will apply it.
+//
+// A wave holds its columns in registers, one entry per lane: row bits 0..5
+// are lane bits (row bit 6 of a 7-qubit matrix is a second register; below 6
+// qubits the lanes above the rows hold further columns), and each lane has
+// kBuildCols consecutive columns. A one-qubit gate is then one exchange with
+// the lane whose index differs in one bit (a DPP move, or a permlane swap for
+// bits 4 and 5) and a complex 2x2 product, a diagonal gate touches the lane's
+// own entry only, and no gate needs a barrier. What bounds the launch is this
+// chain over the gates, so the columns are spread over as many waves as keep
+// kBuildCols of them per lane (4: the entries a lane then holds are
+// neighbours in the fp16-halves layouts, which are written 16 bytes at a
+// time): 16 waves for a 6-qubit matrix, 32 for a 7-qubit one. Measured
+// against one work-group per matrix that held it in LDS with a barrier per
+// gate: 17 us instead of 62 for the 11 matrices of a 20-qubit depth-25
+// circuit, 26 instead of 85 for the 14 of the 30-qubit one, 53 instead of 155
+// for the 634 of a batch of 64 circuits, and 4 / 6 / 9 us instead of 36 / 92 /
+// 190 for a single dense gate of 4 / 5 / 6 qubits.
 constexpr int kBuildThreads = 256;
-constexpr int kBuildCols = 64;  // columns held for k <= 6 (32 for k = 7)
-// entry i of a column: its doubles lie cs apart (the columns side by side)
-__device__ __forceinline__ double& BV(double* v, int i, int cs) { return v[i * cs]; }
+constexpr int kBuildCols = 4;        // columns per lane
+constexpr int kBuildGateChunk = 64;  // gates staged in LDS at a time
 
-__global__ __launch_bounds__(kBuildThreads) void k_build(const BuildOp* __restrict__ ops,
-                                                         const BuildGate* __restrict__ gates,
-                                                         const double* __restrict__ dense, char* __restrict__ mat_base) {
-    // 2 doubles per entry, 2^k entries per column, cs columns: 8192 doubles for k <= 6 and for k = 7
-    __shared__ double Vs[64 * 2 * kBuildCols];
-    __shared__ double Ws[64 * 2 * kBuildCols];
-    const BuildOp op = ops[blockIdx.x];
-    const int k = op.k, D = 1 << k, t = threadIdx.x;
-    const int cs = k == 7 ? 32 : kBuildCols;   // columns held by this work-group
-    const int x0 = k == 7 ? 32 * op.part : 0;  // its first column
-    // thread t: column c, share sub of T
-    const int T = kBuildThreads / cs, c = t % cs, sub = t / cs;
-    const bool act = c < D;
-    double* v = Vs + c;
-    double* w = Ws + c;
-    if (act)
-        for (int i = sub; i < 2 * D; i += T) BV(v, i, cs) = i == 2 * (x0 + c) ? 1.0 : 0.0;
-    __syncthreads();
-    for (int gi = 0; gi < op.n_gates; ++gi) {
-        const BuildGate bg = gates[op.gate0 + gi];
-        if (bg.kind == G_CZ) {
-            const int m = (1 << bg.pos[0]) | (1 << bg.pos[1]);
-            if (act)
-                for (int i = sub; i < D; i += T)
-                    if ((i & m) == m) {
-                        BV(v, 2 * i, cs) = -BV(v, 2 * i, cs);
-                        BV(v, 2 * i + 1, cs) = -BV(v, 2 * i + 1, cs);
-                    }
-        } else if (bg.kind == G_DENSE) {
-            // for each assignment `rest` of the entry bits outside the gate,
-            // the dd entries rest | dep(xl) are multiplied by the gate's
-            // matrix; 16 outputs at a time (one work item, dealt round-robin
-            // to the column's threads) are summed in registers (dep puts bit j
-            // of a gate index at the gate's position j)
-            const int dq = bg.nq, dd = 1 << dq;
-            const double* u = dense + bg.dense_off;
-            int pm = 0;
-            for (int j = 0; j < dq; ++j) pm |= 1 << bg.pos[j];
-            auto dep = [&](int xl) {
-                int o = 0;
-                for (int j = 0; j < dq; ++j) o |= ((xl >> j) & 1) << bg.pos[j];
-                return o;
-            };
-            if (act) {
-                int item = 0;
-                for (int rest = 0; rest < D; rest = ((rest | pm) + 1) & ~pm) {
-                    for (int y0 = 0; y0 < dd; y0 += 16, ++item) {
-                        if (item % T != sub) continue;
-                        double sr[16], si[16];
+// Work-groups per matrix of k qubits (kBuildThreads / 64 waves of
+// kBuildCols * 2^(6-k) columns each; kBuildCols for k = 7).
+__host__ __device__ constexpr int build_parts(int k) { return k <= 5 ? 1 : (k == 6 ? 4 : 8); }
+
+// The value of x in the lane whose index differs in bit B.
+template <int B>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+    if constexpr (B == 0) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true);  // quad [1,0,3,2]
+    if constexpr (B == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true);  // quad [2,3,0,1]
+    if constexpr (B == 2) {  // mirrored within 8 lanes (index ^ 7), then within 4 (^ 3)
+        const int m = __builtin_amdgcn_mov_dpp((int)x, 0x141, 0xf, 0xf, true);
+        return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xf, 0xf, true);
+    }
+    if constexpr (B == 3) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);  // row rotated by 8
+    const int lane = (int)(threadIdx.x & 63);
+    if constexpr (B == 4) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (lane & 16) ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (lane & 32) ? r[0] : r[1];
+    }
+}
+template <int B>
+__device__ __forceinline__ double lane_xor(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = lane_xor<B>((uint32_t)b), hi = lane_xor<B>((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+struct BuildLds {
+    // gates of the current chunk; op: 0 CZ, 1 diagonal one-qubit (phase m[6..7]
+    // on |1>), 2 one-qubit, 3 dense
+    double m[kBuildGateChunk][8];
+    int32_t op[kBuildGateChunk], nq[kBuildGateChunk], off[kBuildGateChunk], pos[kBuildGateChunk][6];
+    // a dense gate's input: entry (row, column of the lane) of each wave
+    double2 v[kBuildThreads / 64][128 * kBuildCols];
+};
+
+// R registers per column: 2 for k = 7 (row bit 6), else 1.
+template <int R>
+__device__ __forceinline__ void build_matrix(const BuildOp& op, int part, const BuildGate* __restrict__ gates,
+                                             const double* __restrict__ dense, char* __restrict__ out, BuildLds& L) {
+    constexpr int C = kBuildCols;
+    const int k = R == 2 ? 7 : op.k, D = 1 << k;
+    const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
+    const int rows = R == 2 ? 64 : D;              // rows on lanes
+    const int yl = lane & (rows - 1);              // row bits held by the lane index
+    const int grp = R == 2 ? 0 : lane >> k;        // which of the slot's columns
+    const int x0 = ((part * (kBuildThreads / 64) + wv) * (R == 2 ? 1 : 64 >> k) + grp) * C;  // the lane's first column
+    double vr[R][C], vi[R][C];
 #pragma unroll
-                        for (int t2 = 0; t2 < 16; ++t2) sr[t2] = si[t2] = 0.0;
-                        for (int xl = 0; xl < dd; ++xl) {
-                            const int src = rest | dep(xl);
-                            const double vr = BV(v, 2 * src, cs), vi = BV(v, 2 * src + 1, cs);
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-                            for (int t2 = 0; t2 < 16; ++t2) {
-                                if (y0 + t2 >= dd) break;
-                                const double mr = u[2 * ((y0 + t2) * dd + xl)], mi = u[2 * ((y0 + t2) * dd + xl) + 1];
-                                sr[t2] += mr * vr - mi * vi;
-                                si[t2] += mr * vi + mi * vr;
-                            }
-                        }
+        for (int c = 0; c < C; ++c) {
+            vr[r][c] = (yl | r << 6) == x0 + c ? 1.0 : 0.0;
+            vi[r][c] = 0.0;
+        }
+    for (int g0 = 0; g0 < op.n_gates; g0 += kBuildGateChunk) {
+        const int ng = min(kBuildGateChunk, op.n_gates - g0);
+        if (g0) __syncthreads();  // the previous chunk has been read
+        if ((int)threadIdx.x < ng) {
+            const int t = (int)threadIdx.x;
+            const BuildGate bg = gates[op.gate0 + g0 + t];
+            L.op[t] = bg.kind == G_CZ ? 0 : (bg.kind == G_DENSE ? 3 : (gate_is_diagonal(bg.kind) ? 1 : 2));
+            L.nq[t] = bg.nq;
+            L.off[t] = bg.dense_off;
 #pragma unroll
-                        for (int t2 = 0; t2 < 16; ++t2) {
-                            if (y0 + t2 >= dd) break;
-                            const int dst = rest | dep(y0 + t2);
-                            BV(w, 2 * dst, cs) = sr[t2];
-                            BV(w, 2 * dst + 1, cs) = si[t2];
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            if (act)
-                for (int i = sub; i < 2 * D; i += T) BV(v, i, cs) = BV(w, i, cs);
-        } else {
+            for (int j = 0; j < 6; ++j) L.pos[t][j] = bg.pos[j];
             double m[8];
-            gate2x2(bg.kind, bg.theta, m);
-            const int a = bg.pos[0], lo = (1 << a) - 1;
-            if (act)
-                for (int pr = sub; pr < D / 2; pr += T) {
-                    const int i = ((pr & ~lo) << 1) | (pr & lo), j = i | (1 << a);
-                    const double ar = BV(v, 2 * i, cs), ai = BV(v, 2 * i + 1, cs), br = BV(v, 2 * j, cs),
-                                 bi = BV(v, 2 * j + 1, cs);
-                    BV(v, 2 * i, cs) = (m[0] * ar - m[1] * ai) + (m[2] * br - m[3] * bi);
-                    BV(v, 2 * i + 1, cs) = (m[0] * ai + m[1] * ar) + (m[2] * bi + m[3] * br);
-                    BV(v, 2 * j, cs) = (m[4] * ar - m[5] * ai) + (m[6] * br - m[7] * bi);
-                    BV(v, 2 * j + 1, cs) = (m[4] * ai + m[5] * ar) + (m[6] * bi + m[7] * br);
-                }
+            gate2x2(bg.kind, bg.theta, m);  // zeros for CZ and dense gates
+#pragma unroll
+            for (int j = 0; j < 8; ++j) L.m[t][j] = m[j];
         }
         __syncthreads();
-    }
-    __syncthreads();
-    // M[y][x] = entry y of column x (a column this work-group holds)
-    auto Mre = [&](int y, int xx) { return Vs[(2 * y) * cs + (xx - x0)]; };
-    auto Mim = [&](int y, int xx) { return Vs[(2 * y + 1) * cs + (xx - x0)]; };
-    // k <= 6 layouts: lane l = t % 64 of the MFMA operand, the (row block,
-    // step) pairs dealt to the 4 waves
-    const int lane = t & 63, wv = t >> 6, NW = kBuildThreads / 64;
-    // entry (R, Kc) of the real-split matrix [[Re, -Im], [Im, Re]]
-    auto Ars = [&](int y, int a, int xx, int b) {
-        const double re = Mre(y, xx), im = Mim(y, xx);
-        return (a == b) ? re : (a == 0 ? -im : im);
-    };
-    char* out = mat_base + op.out_off;
-    if (op.layout == LAYOUT_PLAIN) {
-        const int nc = D < cs ? D : cs;  // columns held
-        for (int e = t; e < D * nc; e += kBuildThreads) {
-            const int y = e / nc, xc = x0 + e % nc;
-            if (op.is_double) {
-                reinterpret_cast<double2*>(out)[y * D + xc] = make_double2(Mre(y, xc), Mim(y, xc));
+        // the next gate's record is read while the current one is applied
+        int nop = L.op[0], np0 = L.pos[0][0], np1 = L.pos[0][1];
+        double nm[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) nm[j] = L.m[0][j];
+        for (int gi = 0; gi < ng; ++gi) {
+            const int kind = __builtin_amdgcn_readfirstlane(nop);
+            const int a = __builtin_amdgcn_readfirstlane(np0), b = __builtin_amdgcn_readfirstlane(np1);
+            double m[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) m[j] = nm[j];
+            const int ni = min(gi + 1, ng - 1);
+            nop = L.op[ni];
+            np0 = L.pos[ni][0];
+            np1 = L.pos[ni][1];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) nm[j] = L.m[ni][j];
+            if (kind == 0) {
+                const int mask = (1 << a) | (1 << b);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const bool neg = ((yl | r << 6) & mask) == mask;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        vr[r][c] = neg ? -vr[r][c] : vr[r][c];
+                        vi[r][c] = neg ? -vi[r][c] : vi[r][c];
+                    }
+                }
+            } else if (kind == 1) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (((yl | r << 6) >> a) & 1) {
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            const double x = vr[r][c], y = vi[r][c];
+                            vr[r][c] = m[6] * x - m[7] * y;
+                            vi[r][c] = m[6] * y + m[7] * x;
+                        }
+                    }
+            } else if (kind == 2) {
+                if (R == 2 && a == 6) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const double ar = vr[0][c], ai = vi[0][c], br = vr[R - 1][c], bi = vi[R - 1][c];
+                        vr[0][c] = (m[0] * ar - m[1] * ai) + (m[2] * br - m[3] * bi);
+                        vi[0][c] = (m[0] * ai + m[1] * ar) + (m[2] * bi + m[3] * br);
+                        vr[R - 1][c] = (m[4] * ar - m[5] * ai) + (m[6] * br - m[7] * bi);
+                        vi[R - 1][c] = (m[4] * ai + m[5] * ar) + (m[6] * bi + m[7] * br);
+                    }
+                } else {
+                    // own and partner coefficients: this row's of the 2x2
+                    const bool hi = (yl >> a) & 1;
+                    const double sr = hi ? m[6] : m[0], si = hi ? m[7] : m[1];
+                    const double pr = hi ? m[4] : m[2], pi = hi ? m[5] : m[3];
+                    auto mix = [&](auto BIT) {
+#pragma unroll
+                        for (int r = 0; r < R; ++r)
+#pragma unroll
+                            for (int c = 0; c < C; ++c) {
+                                const double x = vr[r][c], y = vi[r][c];
+                                const double u = lane_xor<decltype(BIT)::value>(x), w = lane_xor<decltype(BIT)::value>(y);
+                                vr[r][c] = (sr * x - si * y) + (pr * u - pi * w);
+                                vi[r][c] = (sr * y + si * x) + (pr * w + pi * u);
+                            }
+                    };
+                    switch (a) {
+                        case 0: mix(std::integral_constant<int, 0>()); break;
+                        case 1: mix(std::integral_constant<int, 1>()); break;
+                        case 2: mix(std::integral_constant<int, 2>()); break;
+                        case 3: mix(std::integral_constant<int, 3>()); break;
+                        case 4: mix(std::integral_constant<int, 4>()); break;
+                        default: mix(std::integral_constant<int, 5>()); break;
+                    }
+                }
             } else {
-                reinterpret_cast<float2*>(out)[y * D + xc] = make_float2((float)Mre(y, xc), (float)Mim(y, xc));
+                // dense: bit j of the gate's index is row bit pos[j]
+                const int dq = __builtin_amdgcn_readfirstlane(L.nq[gi]), dd = 1 << dq;
+                const double2* u = reinterpret_cast<const double2*>(dense + __builtin_amdgcn_readfirstlane(L.off[gi]));
+                int pm = 0;
+                for (int j = 0; j < dq; ++j) pm |= 1 << __builtin_amdgcn_readfirstlane(L.pos[gi][j]);
+                auto ext = [&](int y) {  // the gate's index of row y
+                    int o = 0;
+                    for (int j = 0; j < dq; ++j) o |= ((y >> __builtin_amdgcn_readfirstlane(L.pos[gi][j])) & 1) << j;
+                    return o;
+                };
+                auto dep = [&](int xl) {
+                    int o = 0;
+                    for (int j = 0; j < dq; ++j) o |= ((xl >> j) & 1) << __builtin_amdgcn_readfirstlane(L.pos[gi][j]);
+                    return o;
+                };
+                if (g0 == 0 && gi == 0) {  // on the basis vectors: the gate's own entries
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const int y = yl | r << 6;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            const int x = x0 + c;
+                            double2 e = make_double2(0.0, 0.0);
+                            if (x < D && ((x ^ y) & ~pm) == 0) e = u[ext(y) * dd + ext(x)];
+                            vr[r][c] = e.x;
+                            vi[r][c] = e.y;
+                        }
+                    }
+                } else {
+                    // every lane reads the inputs of its row from LDS, the same
+                    // address for all rows that agree outside the gate
+                    double2* V = L.v[wv];
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) V[(lane | r << 6) * C + c] = make_double2(vr[r][c], vi[r][c]);
+                    __syncthreads();
+                    const double2* row[R];
+                    int src[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        row[r] = u + ext(yl | r << 6) * dd;
+                        src[r] = (lane | r << 6) & ~pm;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) vr[r][c] = vi[r][c] = 0.0;
+                    }
+#pragma unroll 4
+                    for (int xl = 0; xl < dd; ++xl) {
+                        const int o = dep(xl);
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            const double2 e = row[r][xl];
+                            const double2* in = V + (src[r] | o) * C;
+#pragma unroll
+                            for (int c = 0; c < C; ++c) {
+                                const double2 z = in[c];
+                                vr[r][c] += e.x * z.x - e.y * z.y;
+                                vi[r][c] += e.x * z.y + e.y * z.x;
+                            }
+                        }
+                    }
+                    __syncthreads();  // a following dense gate rewrites the inputs
+                }
             }
         }
+    }
+    if (x0 >= D) return;  // columns beyond the matrix (k < 5); x0 + C <= D otherwise, or D < C
+    const int h = 1 << (k - 1), jm = h - 1;
+    if (op.layout == LAYOUT_PLAIN) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (x0 + c >= D) continue;  // k = 1: two columns
+                const int at = (yl | r << 6) * D + x0 + c;
+                if (op.is_double)
+                    reinterpret_cast<double2*>(out)[at] = make_double2(vr[r][c], vi[r][c]);
+                else
+                    reinterpret_cast<float2*>(out)[at] = make_float2((float)vr[r][c], (float)vi[r][c]);
+            }
     } else if (op.layout == LAYOUT_SPLIT7) {
         // k = 7: fp16 halves of 16 Re M and 16 Im M for v_mfma_f32_32x32x16_f16
         // (k_cluster_f32_split7). Entry (rb, s, lane l, i) of each part:
         // physical row rho = l % 32 of row block rb is amplitude
         // (16 rb + 4 (rho / 8) + rho % 4) | ((rho / 4) % 2) << 6; inner element
         // i of the lanes with l / 32 = hin is amplitude (8 s + i) | hin << 6.
-        // This work-group holds the columns whose bits 5, 6 equal op.part, i.e.
-        // steps s with s / 4 = part % 2 and lanes with l / 32 = part / 2.
-        constexpr int S7 = 8, NP7 = 4 * S7 * 64 * 8;  // halves per part
-        _Float16* A = reinterpret_cast<_Float16*>(out);
-        const int s_lo = 4 * (op.part & 1), hin = op.part >> 1;
-        for (int e = t; e < 4 * 4 * 32 * 8; e += kBuildThreads) {
-            const int i = e & 7, lr = (e >> 3) & 31, sl = (e >> 8) & 3, rb = e >> 10;
-            const int s2 = s_lo + sl, l = lr | (hin << 5), rho = lr;
-            const int y = (16 * rb + 4 * (rho >> 3) + (rho & 3)) | (((rho >> 2) & 1) << 6);
-            const int xin = (8 * s2 + i) | (hin << 6);
-            const float vr = (float)(16.0 * Mre(y, xin)), vi = (float)(16.0 * Mim(y, xin));
-            const _Float16 hr = (_Float16)vr, hi = (_Float16)vi;
-            const size_t at = ((size_t)(rb * S7 + s2) * 64 + l) * 8 + i;
-            A[at] = hr;
-            A[NP7 + at] = (_Float16)(vr - (float)hr);
-            A[2 * NP7 + at] = hi;
-            A[3 * NP7 + at] = (_Float16)(vi - (float)hi);
-        }
-    } else if (op.layout == LAYOUT_MFMA32F) {
-        // entry (rb, s, lane l): row rho = l % 32 of row block rb, inner index 2 s + l / 32
-        const int RB = 2 * D / 32, S = D, l = lane;
-        const int rho = l & 31, hin = l >> 5;
-        float* A = reinterpret_cast<float*>(out);
-        for (int it = wv; it < RB * S; it += NW) {
-            const int rb = it / S, s = it % S;
-            const int jout = rb * 8 + 2 * (rho >> 3) + ((rho & 3) >> 1);
-            const int hout = (rho >> 2) & 1;
-            const int y = jout | (hout << (k - 1)), a = rho & 1;
-            const int xin = (s >> 1) | (hin << (k - 1)), b = s & 1;
-            A[(rb * S + s) * 64 + l] = (float)Ars(y, a, xin, b);
-        }
-    } else if (op.layout == LAYOUT_GAUSS32F) {
-        // k = 6: three 64 x 64 real matrices P = 0: Re M, 1: Im M, 2: Re M + Im M,
-        // for v_mfma_f32_16x16x4_f32. Entry (P, rb, s, lane l): physical row
-        // i = l % 16 of row block rb, inner index s | (l / 16) << 4. The result
-        // of physical row i lands in register i % 4 of the lanes with l / 16 =
-        // i / 4, which own amplitude (4 rb + i % 4) | (i / 4) << 4.
-        const int l = lane, i = l & 15, qin = l >> 4;
-        float* A = reinterpret_cast<float*>(out);
-        for (int it = wv; it < 4 * 16; it += NW) {
-            const int rb = it / 16, s2 = it % 16;
-            const int y = (4 * rb + (i & 3)) | ((i >> 2) << 4);
-            const int xin = s2 | (qin << 4);
-            const double re = Mre(y, xin), im = Mim(y, xin);
-            A[((0 * 4 + rb) * 16 + s2) * 64 + l] = (float)re;
-            A[((1 * 4 + rb) * 16 + s2) * 64 + l] = (float)im;
-            A[((2 * 4 + rb) * 16 + s2) * 64 + l] = (float)(re + im);
+        // The lane's columns are four neighbouring i.
+        if constexpr (R == 2) {
+            typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+            constexpr int S7 = 8, NP7 = 4 * S7 * 64 * 8;  // halves per part
+            _Float16* A = reinterpret_cast<_Float16*>(out);
+            const int s = (x0 & 63) >> 3, i = x0 & 7, hin = x0 >> 6;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int rb = lane >> 4, q = lane & 15, rho = ((q >> 2) << 3) | (r << 2) | (q & 3);
+                half4v p[4];
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const float fr = (float)(16.0 * vr[r][c]), fi = (float)(16.0 * vi[r][c]);
+                    p[0][c] = (_Float16)fr;
+                    p[1][c] = (_Float16)(fr - (float)p[0][c]);
+                    p[2][c] = (_Float16)fi;
+                    p[3][c] = (_Float16)(fi - (float)p[2][c]);
+                }
+                const int at = ((rb * S7 + s) * 64 + (rho | hin << 5)) * 8 + i;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) *reinterpret_cast<half4v*>(A + w * NP7 + at) = p[w];
+            }
         }
     } else if (op.layout == LAYOUT_SPLIT16F) {
         // k = 5 or 6, fp16 halves of 16 x the real-split matrix for
@@ -3229,38 +3327,95 @@ __global__ __launch_bounds__(kBuildThreads) void k_build(const BuildOp* __restri
         // l % 32 of row block rb (result rows as in LAYOUT_MFMA32F), inner index
         // float 8 s + i of the lanes with l / 32 = hin, i.e. component i % 2 of
         // amplitude (4 s + i / 2) | hin << (k - 1). hi block, then lo block.
-        const int l = lane, rho = l & 31, hin = l >> 5;
+        // The lane's four columns are the eight i of one entry.
+        typedef _Float16 half8v __attribute__((ext_vector_type(8)));
         const int RB = 1 << (k - 4), S = 1 << (k - 3);
-        _Float16* Ahi = reinterpret_cast<_Float16*>(out);
-        _Float16* Alo = Ahi + (size_t)RB * S * 64 * 8;
-        for (int it = wv; it < RB * S; it += NW) {
-            const int rb = it / S, s2 = it % S;
-            const int jout = rb * 8 + 2 * (rho >> 3) + ((rho & 3) >> 1);
-            const int hout = (rho >> 2) & 1;
-            const int y = jout | (hout << (k - 1)), a = rho & 1;
-            for (int i = 0; i < 8; ++i) {
-                const int xin = (4 * s2 + (i >> 1)) | (hin << (k - 1)), b = i & 1;
-                const float v = (float)(16.0 * Ars(y, a, xin, b));
-                const _Float16 hi = (_Float16)v;
-                const size_t at = ((size_t)(rb * S + s2) * 64 + l) * 8 + i;
-                Ahi[at] = hi;
-                Alo[at] = (_Float16)(v - (float)hi);
-            }
+        const int y = yl, hout = y >> (k - 1), j = y & jm, rb = j >> 3;
+        const int rho0 = (((j >> 1) & 3) << 3) | (hout << 2) | ((j & 1) << 1);
+        const int hin = x0 >> (k - 1), s = (x0 & jm) >> 2;
+        half8v* Ahi = reinterpret_cast<half8v*>(out);
+        half8v* Alo = Ahi + RB * S * 64;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {  // row [Re, -Im] or [Im, Re] of the entry
+            half8v hi, lo;
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const float f = (float)(16.0 * (a == b ? vr[0][c] : (a == 0 ? -vi[0][c] : vi[0][c])));
+                    hi[2 * c + b] = (_Float16)f;
+                    lo[2 * c + b] = (_Float16)(f - (float)hi[2 * c + b]);
+                }
+            const int at = (rb * S + s) * 64 + (rho0 | a | hin << 5);
+            Ahi[at] = hi;
+            Alo[at] = lo;
+        }
+    } else if (op.layout == LAYOUT_MFMA32F) {
+        // entry (rb, s, lane l): physical row rho = l % 32 of row block rb is
+        // component rho % 2 of amplitude (8 rb + 2 (rho / 8) + (rho / 2) % 2) |
+        // ((rho / 4) % 2) << (k - 1); inner index s of the lanes with l / 32 =
+        // hin is component s % 2 of amplitude (s / 2) | hin << (k - 1)
+        const int S = D, y = yl, hout = y >> (k - 1), j = y & jm, rb = j >> 3;
+        const int rho0 = (((j >> 1) & 3) << 3) | (hout << 2) | ((j & 1) << 1);
+        float* A = reinterpret_cast<float*>(out);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int x = x0 + c, hin = x >> (k - 1), s = 2 * (x & jm);
+            float* e = A + (rb * S + s) * 64 + (rho0 | hin << 5);
+            e[0] = (float)vr[0][c];
+            e[64] = (float)-vi[0][c];
+            e[1] = (float)vi[0][c];
+            e[65] = (float)vr[0][c];
+        }
+    } else if (op.layout == LAYOUT_GAUSS32F) {
+        // k = 6: three 64 x 64 real matrices P = 0: Re M, 1: Im M, 2: Re M + Im M,
+        // for v_mfma_f32_16x16x4_f32. Entry (P, rb, s, lane l): physical row
+        // i = l % 16 of row block rb, inner index s | (l / 16) << 4. The result
+        // of physical row i lands in register i % 4 of the lanes with l / 16 =
+        // i / 4, which own amplitude (4 rb + i % 4) | (i / 4) << 4.
+        const int i = (yl & 3) | ((yl >> 4) << 2), rb = (yl >> 2) & 3;
+        float* A = reinterpret_cast<float*>(out);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int x = x0 + c, s = x & 15, l = i | ((x >> 4) << 4);
+            A[((0 * 4 + rb) * 16 + s) * 64 + l] = (float)vr[0][c];
+            A[((1 * 4 + rb) * 16 + s) * 64 + l] = (float)vi[0][c];
+            A[((2 * 4 + rb) * 16 + s) * 64 + l] = (float)(vr[0][c] + vi[0][c]);
         }
     } else {  // LAYOUT_MFMA16D
-        // entry (rb, s, lane l): row rho = l % 16 of row block rb, inner index 4 s + l / 16.
-        // The result row rho lands in register rho / 4 of the lanes with l / 16 = rho % 4.
-        const int RB = 2 * D / 16, S = 2 * D / 4, l = lane;
-        const int rho = l & 15, qin = l >> 4;
+        // entry (rb, s, lane l): physical row rho = l % 16 of row block rb, inner
+        // index 4 s + l / 16: component (rho / 4) % 2 of amplitude
+        // (2 rb + rho / 8) | (rho % 4) << (k - 2) (result row rho lands in register
+        // rho / 4 of the lanes with l / 16 = rho % 4), and component s % 2 of
+        // amplitude (s / 2) | (l / 16) << (k - 2)
+        const int S = 2 * D / 4, qm = (1 << (k - 2)) - 1;
+        const int y = yl, qout = y >> (k - 2), j = y & qm, rb = j >> 1;
         double* A = reinterpret_cast<double*>(out);
-        for (int it = wv; it < RB * S; it += NW) {
-            const int rb = it / S, s = it % S;
-            const int qout = rho & 3, ir = rho >> 2;
-            const int y = (rb * 2 + (ir >> 1)) | (qout << (k - 2)), a = ir & 1;
-            const int xin = (s >> 1) | (qin << (k - 2)), b = s & 1;
-            A[(rb * S + s) * 64 + l] = Ars(y, a, xin, b);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int x = x0 + c, qin = x >> (k - 2), s = 2 * (x & qm);
+            const int rho = ((j & 1) << 3) | qout;  // component 0 of the row; component 1: rho | 4
+            double* e = A + (rb * S + s) * 64 + (rho | qin << 4);
+            e[0] = vr[0][c];
+            e[64] = -vi[0][c];
+            e[4] = vi[0][c];
+            e[68] = vr[0][c];
         }
     }
+}
+
+__global__ __launch_bounds__(kBuildThreads) void k_build(const BuildOp* __restrict__ ops,
+                                                         const BuildGate* __restrict__ gates,
+                                                         const double* __restrict__ dense, char* __restrict__ mat_base) {
+    __shared__ BuildLds L;
+    const BuildOp op = ops[blockIdx.x];
+    const int part = (int)blockIdx.y;
+    if (part >= build_parts(op.k)) return;  // the grid is sized for the widest matrix
+    char* out = mat_base + op.out_off;
+    if (op.k == 7)
+        build_matrix<2>(op, part, gates, dense, out, L);
+    else
+        build_matrix<1>(op, part, gates, dense, out, L);
 }
 
 // ------------------------------------------------------------ float64 reductions
@@ -3543,10 +3698,11 @@ hipError_t launch_init_cluster(void* psi, bool dbl, const ClusterGeom& g, const 
     return hipGetLastError();
 }
 
-hipError_t launch_build(const BuildOp* ops, int n_ops, const BuildGate* gates, const double* dense,
+hipError_t launch_build(const BuildOp* ops, int n_ops, int kmax, const BuildGate* gates, const double* dense,
                         char* mat_base, hipStream_t st) {
     if (n_ops <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_build, dim3(n_ops), dim3(kBuildThreads), 0, st, ops, gates, dense, mat_base);
+    hipLaunchKernelGGL(k_build, dim3(n_ops, build_parts(kmax)), dim3(kBuildThreads), 0, st, ops, gates, dense,
+                       mat_base);
     return hipGetLastError();
 }
 
