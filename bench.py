@@ -42,26 +42,48 @@ def kernel_source_hash() -> str:
 
 def kernel_name(rec, k6_kernel=2, pair_tile=11, dbl=False, n=None) -> str:
     """Name (as rocprofv3 reports it) of the cluster kernel a launch used (n:
-    the state's qubits, which decide the vector-ALU kernel's form)."""
+    the state's qubits, which decide the kernel's form; without it the kernel's
+    plain name)."""
     k, lowt = rec["k"], rec["qubits"][0] == 0
     staged_valu = n is not None and 2 <= k <= 3 and n - k >= 6 and not rec.get("mfma")
+    # a state of 512 MiB and more: non-temporal accesses, where they cover whole 128-byte lines
+    far = n is not None and n + (4 if dbl else 3) >= 29
+    b = lambda x: "true" if x else "false"  # noqa: E731
+    first = lambda i, bits: len(rec["qubits"]) > i and rec["qubits"][i] >= bits  # noqa: E731
     if dbl:
         if not rec.get("mfma"):
+            if n is not None and 2 <= k <= 3 and n - k >= 6 and not far:
+                return "k_cluster_valu_cached<double, %d>" % k
             return ("k_cluster_valu_staged<double, %d, false>" if staged_valu else "k_cluster_valu<double, %d>") % k
+        if k == 6:
+            return "k_cluster_f64_mfma_loop<6, 1, 512>" if n is not None else "k_cluster_f64_mfma<6, 1, 512>"
         if rec.get("staged"):
-            return "k_cluster_f64_stage<%d, 5, %d>" % (k, 512 if k == 5 else 256)
-        return "k_cluster_f64_mfma<%d, %d, %d>" % (k, 1 if k == 6 else 2, 512 if k == 6 else 256)
+            return ("k_cluster_f64_stage<%d, %d, %s>" % (k, 4 if k == 5 else 5, b(far)) if n is not None
+                    else "k_cluster_f64_stage<%d, 5, %d>" % (k, 512 if k == 5 else 256))
+        if n is not None:
+            return "k_cluster_f64_mfma<%d, %d, %s>" % (k, 1 if k == 5 else 2, b(far and first(0, 3)))
+        return "k_cluster_f64_mfma<%d, 2, 256>" % k
     if rec["kind"] == "pair":
         q = set(rec["qubits"])
         ten = pair_tile == 10 and (0 in q or len(q) < 10)  # the 10-qubit tile holds qubit 0
         return "k_cluster_f32_pair10<12>" if ten else "k_cluster_f32_multi<2, 8>"
-    b = lambda x: "true" if x else "false"  # noqa: E731
+    if staged_valu and not far and not rec.get("stats"):
+        return "k_cluster_valu_cached<float, %d>" % k
     if staged_valu:  # its second flag sums the reductions
         return "k_cluster_valu_staged<float, %d, %s>" % (k, b(rec.get("stats")))
     if not rec.get("mfma"):
         return "k_cluster_valu<float, %d>" % k
     if k == 7:  # the direct kernel only; its second flag sums the reductions
         return "k_cluster_f32_split7<%s, %s>" % (b(lowt), b(rec.get("stats")))
+    if n is not None and k6_kernel == 2 and (k == 6 or k == 5 and n >= 11 or k == 4 and far):
+        # 4 and 5 qubits are padded to 6, with qubits above the lowest five others
+        if rec.get("staged"):
+            return "k_cluster_f32_split6s<%s, %s>" % (b(lowt), b(far))
+        if rec.get("stats"):
+            return "k_cluster_f32_split6_sum<%s>" % b(lowt)
+        own = rec["qubits"][:k]
+        pads = [q for q in range(n) if q not in own][5:5 + 6 - k]
+        return "k_cluster_f32_split6<%s, %s>" % (b(lowt), b(far and sorted(own + pads)[1] >= 4))
     if k == 6 and k6_kernel in (1, 2):
         if k6_kernel == 2 and rec.get("staged"):
             return "k_cluster_f32_split6s<%s>" % b(lowt)

@@ -253,6 +253,8 @@ struct Chunk {
         int variant;     // kind 0: matrix-core kernel variant chosen by the learned model, -1: the library's rule
         int omask, rmask;  // kind 8: the table form's shared and sign-flipped rows, omask -1: matrix cores
         int slot3;         // kind 8 table form: the table's slot
+        int k;             // kind 0: the cluster's own qubits (geom has those its matrix is padded to)
+        int qubits[kMaxK];
     };
     std::vector<Item> items;
     int slots_used = 0;
@@ -330,8 +332,8 @@ qsim_status flush(qsim_state_s* s, Chunk& c) {
         const int variant =
             it.kind == 0 ? (it.variant >= 0 ? it.variant : cluster_variant_for(s->dbl, it.geom, it.layout)) : 0;
         if (it.kind == 0 || it.kind == 6 || it.kind == 7 || it.kind == 8) {
-            r.k = it.geom.k;
-            for (int j = 0; j < it.geom.k; ++j) r.qubits[j] = it.geom.t[j];
+            r.k = it.kind == 0 ? it.k : it.geom.k;
+            for (int j = 0; j < r.k; ++j) r.qubits[j] = it.kind == 0 ? it.qubits[j] : it.geom.t[j];
             r.flags = (it.epi >= 0 ? 1 : 0) | (variant == 1 ? 2 : 0) | (it.layout != LAYOUT_PLAIN ? 4 : 0) |
                       (it.stats ? 8 : 0) | (it.kind == 8 && it.omask >= 0 ? 16 : 0) | (std::min(it.n_epi, 255) << 8);
         } else if (it.kind >= 2) {
@@ -424,16 +426,34 @@ qsim_status add_cluster(qsim_state_s* s, Chunk& c, int k, const int* qubits, con
         qsim_status r = flush(s, c);
         if (r != QSIM_OK) return r;
     }
+    int layout = fold_init ? LAYOUT_PLAIN : cluster_layout(s->dbl, k, s->n);
+    if (layout < 0) return fail(QSIM_E_UNSUPPORTED, "no kernel for a cluster of this width on this state");
+    // clusters of 4 and 5 qubits on the 6-qubit fp16-halves kernel: identity on
+    // the lowest qubits above the five column bits of its tile, which leaves the
+    // tile's contiguous runs as they are (a workspace with slots too small for a
+    // 6-qubit matrix keeps the fp32 kernels)
+    int t[kMaxK], kt = k;
+    for (int j = 0; j < k; ++j) t[j] = qubits[j];
+    if (layout == LAYOUT_SPLIT16F && k < 6) {
+        if (s->kmax_ws >= 6) {
+            uint64_t own = 0;
+            for (int j = 0; j < k; ++j) own |= uint64_t(1) << qubits[j];
+            for (int b = 0, free = 0; b < s->n && kt < 6; ++b)
+                if (!(own >> b & 1) && ++free > 5) t[kt++] = b;
+            std::sort(t, t + kt);
+        } else {
+            layout = LAYOUT_MFMA32F;
+        }
+    }
     int pos_of[64];
     for (int i = 0; i < 64; ++i) pos_of[i] = -1;
-    for (int j = 0; j < k; ++j) pos_of[qubits[j]] = j;
+    for (int j = 0; j < kt; ++j) pos_of[t[j]] = j;
     BuildOp bo;
     std::memset(&bo, 0, sizeof(bo));
-    bo.k = k;
+    bo.k = kt;
     bo.gate0 = (int)c.bgates.size();
     bo.is_double = fold_init ? 1 : s->dbl;
-    bo.layout = fold_init ? LAYOUT_PLAIN : cluster_layout(s->dbl, k, s->n);
-    if (bo.layout < 0) return fail(QSIM_E_UNSUPPORTED, "no kernel for a cluster of this width on this state");
+    bo.layout = layout;
     bo.out_off = (int64_t)c.slots_used * (int64_t)slot_bytes(s->dbl, s->kmax_ws);
     for (int gi : members) c.bgates.push_back(to_build_gate(gates[gi], pos_of, c.dense));
     // epilogue: terms on target qubits only join the matrix, the rest go to the descriptor
@@ -444,10 +464,12 @@ qsim_status add_cluster(qsim_state_s* s, Chunk& c, int k, const int* qubits, con
     Chunk::Item it;
     std::memset(&it, 0, sizeof(it));
     it.kind = fold_init ? 6 : 0;
-    for (int j = 0; j < k; ++j) it.geom.t[j] = qubits[j];
+    it.k = k;
+    for (int j = 0; j < k; ++j) it.qubits[j] = qubits[j];
+    for (int j = 0; j < kt; ++j) it.geom.t[j] = t[j];
     it.geom.n = s->n;
-    it.geom.k = k;
-    it.geom.ncols = uint64_t(1) << (s->n - k);
+    it.geom.k = kt;
+    it.geom.ncols = uint64_t(1) << (s->n - kt);
     it.layout = bo.layout;
     it.slot = c.slots_used++;
     it.epi = -1;
@@ -846,14 +868,21 @@ qsim_status qsim_apply_diag(qsim_state s, int n_pairs, const int32_t* cz_pairs, 
 
 namespace {
 // Tile geometry of a bit permutation (m <= kPermMaxBits moving locations):
-// the moving locations and the lowest fixed ones, up to 12 bits, so loads
-// and stores run over the lowest bits.
-PermGeom perm_geom(int n, int m, const int32_t* from, const int32_t* to) {
+// the moving locations and the lowest fixed ones, so loads and stores run
+// over the lowest bits. 12 bits; 13 (64 KiB of LDS) when those leave out one of
+// a complex64 state's lowest four, which make up a cache line (28 qubits, the
+// twelve highest locations: 2.3 ms against 3.8 ms; with whole lines in the tile
+// the smaller one lets more work-groups in flight: 24 qubits, 46 against 72 us).
+// Bit 0 is then always a tile bit: a 16-byte access takes two amplitudes.
+PermGeom perm_geom(int n, bool dbl, int m, const int32_t* from, const int32_t* to) {
     PermGeom pg{};
     uint64_t tile = 0;
     for (int j = 0; j < m; ++j) tile |= uint64_t(1) << from[j];
-    const int nt = std::min(n, kPermMaxBits);
-    for (int b = 0; b < n && __builtin_popcountll(tile) < nt; ++b) tile |= uint64_t(1) << b;
+    auto grow = [&](int nt) {
+        for (int b = 0; b < n && __builtin_popcountll(tile) < nt; ++b) tile |= uint64_t(1) << b;
+    };
+    grow(std::min(n, kPermTileBits - 1));
+    if (!dbl && (tile & 15) != 15) grow(std::min(n, kPermTileBits));
     int tau_of[64];
     for (int b = 0; b < n; ++b)
         if (tile >> b & 1) {
@@ -916,7 +945,7 @@ qsim_status qsim_permute_qubits(qsim_state s, int m, const int32_t* from, const 
     for (int j = 0; j < m; ++j) identity &= from[j] == to[j];
     if (identity) return QSIM_OK;
     s->stats_ready = false;
-    HIP_TRY(launch_permute(s->psi, s->dbl, s->n, perm_geom(s->n, m, from, to), s->st), "permute launch");
+    HIP_TRY(launch_permute(s->psi, s->dbl, s->n, perm_geom(s->n, s->dbl, m, from, to), s->st), "permute launch");
     return QSIM_OK;
 }
 
@@ -1074,7 +1103,7 @@ qsim_status qsim_run_circuit(qsim_state s, const qsim_gate* gates, int n_gates, 
         r.k = pm;
         for (int j = 0; j < std::min(pm, kMaxK); ++j) r.qubits[j] = pto[j];
         HIP_TRY(rec_begin(s, r), "event record");
-        HIP_TRY(launch_permute(s->psi, s->dbl, s->n, perm_geom(s->n, pm, pfrom, pto), s->st), "permute launch");
+        HIP_TRY(launch_permute(s->psi, s->dbl, s->n, perm_geom(s->n, s->dbl, pm, pfrom, pto), s->st), "permute launch");
         HIP_TRY(rec_end(s, r), "event record");
         st.n_ops++;
     }

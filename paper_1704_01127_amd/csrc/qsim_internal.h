@@ -97,7 +97,8 @@ enum : int32_t {
     LAYOUT_MFMA32F = 1,   // real-split, permuted for v_mfma_f32_32x32x2_f32
     LAYOUT_MFMA16D = 2,   // real-split, permuted for v_mfma_f64_16x16x4_f64
     LAYOUT_GAUSS32F = 3,  // k = 6 float: Re M, Im M, Re M + Im M (three-product complex matrix)
-    LAYOUT_SPLIT16F = 4,  // k = 6 float: fp16 hi / lo halves of 16 x the real-split matrix
+    LAYOUT_SPLIT16F = 4,  // k = 6 float (5, and 4 beyond the caches, padded to 6): fp16 hi / lo halves of 16 x
+                          // the real-split matrix
     LAYOUT_SPLIT7 = 5     // k = 7 float: fp16 hi / lo halves of 16 x Re M and 16 x Im M
 };
 
@@ -128,7 +129,7 @@ struct StageGeom {
     int32_t nt;          // tile bits (k + C)
     int32_t tb[16];      // their state-bit positions, ascending
     int32_t tpos[6];     // tau bit of target m
-    int32_t cpos[6];     // tau bit of column bit b
+    int32_t cpos[9];     // tau bit of column bit b
     int32_t swz[6];      // 6-qubit staged loop: LDS slot of tau = tau ^ (XOR of swz[i] over set bits 5 + i)
     uint64_t ioff[32];   // state offset of linear chunk i (tau = i << lane_bits ...)
 };
@@ -175,6 +176,10 @@ inline int64_t matrix_bytes(int k, int layout, bool dbl) {
     if (layout == LAYOUT_SPLIT7) return 4 * d * d * 2;
     return (2 * d) * (2 * d) * es;
 }
+
+// Is a state of 2^n amplitudes larger than what the last-level cache (256 MiB)
+// keeps from one pass to the next? From 512 MiB on.
+inline bool beyond_caches(int n, bool dbl) { return n + (dbl ? 4 : 3) >= 29; }
 
 // Largest cluster a state can take: 7 qubits on complex64 states of at least
 // 12 qubits (a wave tile is 32 columns of 2^7 amplitudes) while 6-qubit
@@ -267,11 +272,12 @@ hipError_t launch_cz(void* psi, bool dbl, int n, int a, int b, hipStream_t st);
 // tb[0..nt) (ascending state bit positions) vary; tau is the index inside a
 // tile (bit j of tau at state bit tb[j]). The amplitude at tile index tau
 // moves to the tile index whose bit to[j] is bit j of tau.
-constexpr int kPermMaxBits = 12;
+constexpr int kPermMaxBits = 12;  // moving locations
+constexpr int kPermTileBits = 13; // largest tile
 struct PermGeom {
     int32_t nt;
-    int32_t tb[kPermMaxBits];
-    int32_t to[kPermMaxBits];
+    int32_t tb[kPermTileBits];
+    int32_t to[kPermTileBits];
 };
 hipError_t launch_permute(void* psi, bool dbl, int n, const PermGeom& pg, hipStream_t st);
 

@@ -19,6 +19,21 @@
 // so that every lane's MFMA operands and results are exactly the amplitudes
 // it loads and stores: lane (p, h) of a float wave owns the amplitudes whose
 // highest target bit is h in column p, with no LDS round trip for the state.
+//
+// How the kernels walk the state. A pass is bound by HBM, and what DRAM gives
+// depends on how compact the stretch of the state in flight is. Most kernels
+// therefore do one tile per wave, work-groups in memory order: the hardware
+// hands the next tiles to whichever compute unit is free, so the tiles in
+// flight stay next to each other. Waves of a persistent grid drift apart (an
+// in-place linear pass over 8 GiB: 3.0 ms against 3.4 ms, a 64-row gather of
+// 256-byte runs 3.2-3.3 against 3.5-3.8), also when each takes its own
+// contiguous share (3.3 ms for 2 MiB per work-group). The matrix is then read
+// from L2 once per work-group, which costs less than it gains. A state beyond
+// the 256 MiB last-level cache is moved with non-temporal accesses, another
+// 5-10 % (linear: 2.65 ms = 6.5 TB/s); a smaller one is not, since the next
+// pass finds it in the cache (25 qubits complex64: 90 us against 101 us with
+// them), and neither are accesses that cover a 128-byte line only in part
+// (a 6-qubit cluster on qubits 0-5 gathered directly: 24 ms against 4.6 ms).
 #include "qsim_internal.h"
 
 #include <cmath>
@@ -185,6 +200,20 @@ typedef const QSIM_GLOBAL EpiDesc g_epi;
 // and waiting for them would wait for the whole prefetch.)
 typedef const __attribute__((address_space(4))) EpiDesc c_epi;
 
+// 16-byte accesses of the state; NT: past the caches (non-temporal).
+template <bool NT, typename V>
+__device__ __forceinline__ V load16(const V* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    return *p;
+}
+template <bool NT, typename V>
+__device__ __forceinline__ void store16(V* p, V v) {
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 // Copy a cluster matrix of N elements into LDS: 16-byte loads, all in flight
 // before the first LDS store (a loop of single loads would wait for each).
 template <int N, int THREADS, typename T, typename V4>
@@ -202,6 +231,53 @@ __device__ __forceinline__ void load_matrix(T* __restrict__ dst, const V4* __res
 #pragma unroll
     for (int i = 0; i < PER; ++i) reinterpret_cast<v4*>(dst)[threadIdx.x + i * THREADS] = r[i];
     if (REST && threadIdx.x < REST) reinterpret_cast<v4*>(dst)[PER * THREADS + threadIdx.x] = t;
+}
+
+// The same in two steps, for a kernel that has other loads to issue in
+// between: the loads of BYTES of matrix at construction, the LDS stores later.
+template <int BYTES, int THREADS>
+struct MatrixRegs {
+    static constexpr int CHUNKS = BYTES / 16, PER = CHUNKS / THREADS, REST = CHUNKS % THREADS;
+    static_assert(BYTES % 16 == 0, "matrix is a whole number of 16-byte chunks");
+    vf4 r[PER > 0 ? PER : 1], t;
+    __device__ __forceinline__ explicit MatrixRegs(const void* src) {
+        const vf4* m = reinterpret_cast<const vf4*>(src);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) r[i] = m[i * THREADS + threadIdx.x];
+        if (REST && threadIdx.x < REST) t = m[PER * THREADS + threadIdx.x];
+    }
+    __device__ __forceinline__ void store(void* dst) const {
+        vf4* m = reinterpret_cast<vf4*>(dst);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) m[i * THREADS + threadIdx.x] = r[i];
+        if (REST && threadIdx.x < REST) m[PER * THREADS + threadIdx.x] = t;
+    }
+};
+
+// The value of x in the lane whose index differs in bit B.
+template <int B>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+    if constexpr (B == 0) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true);  // quad [1,0,3,2]
+    if constexpr (B == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true);  // quad [2,3,0,1]
+    if constexpr (B == 2) {  // mirrored within 8 lanes (index ^ 7), then within 4 (^ 3)
+        const int m = __builtin_amdgcn_mov_dpp((int)x, 0x141, 0xf, 0xf, true);
+        return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xf, 0xf, true);
+    }
+    if constexpr (B == 3) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);  // row rotated by 8
+    const int lane = (int)(threadIdx.x & 63);
+    if constexpr (B == 4) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (lane & 16) ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (lane & 32) ? r[0] : r[1];
+    }
+}
+template <int B>
+__device__ __forceinline__ double lane_xor(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = lane_xor<B>((uint32_t)b), hi = lane_xor<B>((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 
 // ------------------------------------------------------------ cluster: MFMA, float
@@ -555,10 +631,103 @@ __device__ __forceinline__ int split_halves(const float (&X)[N], half8 (&xh)[N /
 }
 
 
-// STATS: as in k_cluster_f32_mfma (sums of the stored amplitudes' p, p^2,
-// -p ln p into part, per work-group).
-template <bool LOWT, bool STATS = false>
+// Swap a (in the odd 16-lane rows of the wave) with b (in the even rows):
+// afterwards lane l of an even row holds in b what lane l + 16 held in a, and
+// lane l + 16 holds in a what lane l held in b.
+__device__ __forceinline__ void lane_swap16(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
+// One wave tile per wave, work-groups in memory order; NT: a state beyond the
+// caches. Bound by HBM (the product takes about half of the pass). 30 qubits,
+// 23 target sets: 3.0 ms per pass (5.7 TB/s) where accesses cover whole lines,
+// 3.45 ms as a persistent grid with 8-byte accesses.
+template <bool LOWT, bool NT>
 __global__ __launch_bounds__(256, 2) void k_cluster_f32_split6(float2* __restrict__ psi,
+                                                               const half8* __restrict__ Ap,
+                                                               const EpiDesc* __restrict__ epi,
+                                                               ClusterGeom g) {
+    constexpr int K = 6, HX = 32, RB = 4, S = 8, NP = RB * S * 64;
+    __shared__ half8 L[2 * NP];  // hi, lo
+    const int lane = threadIdx.x & 63, p = lane & 31, h = lane >> 5;
+    // without a target on qubit 0, lanes p and p + 16 hold neighbouring
+    // columns and access both as 16 bytes, even rows in the lower lane, odd
+    // rows in the upper (as in k_cluster_f32_split7)
+    constexpr bool PAIR = !LOWT;
+    const int cpair = PAIR ? 2 * (p & 15) : p;
+    const uint64_t cown = PAIR ? (uint64_t)((p >> 4) & 1) : 0;
+    const uint64_t tile = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint64_t base = deposit_cols<K>(tile * 32 + cpair, g);
+    const uint64_t b0 = base | (h ? uint64_t(1) << g.t[K - 1] : 0) | (cown ? uint64_t(1) << g.t[0] : 0);
+    float X[2 * HX];
+    MatrixRegs<2 * NP * 16, 256> mr(Ap);
+    const bool act = tile < g.ncols / 32;
+    if (act) {
+#pragma unroll
+        for (int j = 0; j < HX; j += 2) {
+            const vf4* q = reinterpret_cast<const vf4*>(psi + (b0 | target_off<K - 1>(j, g)));
+            const vf4 v = load16<NT>(q);
+            X[2 * j] = v.x; X[2 * j + 1] = v.y; X[2 * j + 2] = v.z; X[2 * j + 3] = v.w;
+        }
+    }
+    mr.store(L);
+    __syncthreads();
+    if (!act) return;
+    if constexpr (PAIR) {  // rows j, j + 1 of the lane's own column
+#pragma unroll
+        for (int j = 0; j < HX; j += 2) {
+            lane_swap16(X[2 * j], X[2 * j + 2]);
+            lane_swap16(X[2 * j + 1], X[2 * j + 3]);
+        }
+    }
+    half8 xh[S], xl[S];
+    const float unscale = __builtin_ldexpf(1.0f, -split_halves<2 * HX>(X, xh, xl) - 4);
+    floatx16 acc[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[rb][i] = 0.0f;
+#pragma unroll
+    for (int st = 0; st < S; ++st) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const half8 ah = L[(rb * S + st) * 64 + lane];
+            const half8 al = L[NP + (rb * S + st) * 64 + lane];
+            acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, xl[st], acc[rb], 0, 0, 0);
+            acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, xh[st], acc[rb], 0, 0, 0);
+            acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, xh[st], acc[rb], 0, 0, 0);
+        }
+    }
+    float O[2 * HX];
+#pragma unroll
+    for (int j = 0; j < 2 * HX; ++j) O[j] = acc[j / 16][j % 16] * unscale;
+    if (epi != nullptr) {
+        const ColFactor<float> f = col_factor<float>((c_epi*)epi, base | cown);
+        const bool has_ph = epi->n_ph > 0;
+#pragma unroll
+        for (int j = 0; j < HX; ++j)
+            apply_factor(O[2 * j], O[2 * j + 1], f, (uint32_t)(j | (h << (K - 1))), has_ph);
+    }
+#pragma unroll
+    for (int j = 0; j < HX; j += 2) {
+        if constexpr (PAIR) {  // row j of both columns (lower lane), row j + 1 (upper)
+            lane_swap16(O[2 * j], O[2 * j + 2]);
+            lane_swap16(O[2 * j + 1], O[2 * j + 3]);
+        }
+        vf4* q = reinterpret_cast<vf4*>(psi + (b0 | target_off<K - 1>(j, g)));
+        const vf4 v{O[2 * j], O[2 * j + 1], O[2 * j + 2], O[2 * j + 3]};
+        store16<NT>(q, v);
+    }
+}
+
+// The last op of a run whose sums are wanted: as the STATS form of
+// k_cluster_f32_mfma, it also sums the stored amplitudes' p, p^2 and -p ln p
+// into part, per work-group. Persistent, since the partials of one work-group
+// per tile would not fit their area; the next tile is prefetched.
+template <bool LOWT>
+__global__ __launch_bounds__(256, 2) void k_cluster_f32_split6_sum(float2* __restrict__ psi,
                                                                const half8* __restrict__ Ap,
                                                                const EpiDesc* __restrict__ epi,
                                                                ClusterGeom g, double* __restrict__ part) {
@@ -581,7 +750,7 @@ __global__ __launch_bounds__(256, 2) void k_cluster_f32_split6(float2* __restric
     uint64_t tile = (uint64_t)xcd_block() * 4 + (threadIdx.x >> 6);
     double sv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (tile >= ntiles) {  // uniform in the wave: every wave reaches one reduction
-        if constexpr (STATS) block_reduce_store(sv, 3, 0u, part + blockIdx.x * 8);
+        block_reduce_store(sv, 3, 0u, part + blockIdx.x * 8);
         return;
     }
     const uint64_t last = ntiles - 1;
@@ -636,16 +805,14 @@ __global__ __launch_bounds__(256, 2) void k_cluster_f32_split6(float2* __restric
             for (int j = 0; j < HX; ++j)
                 apply_factor(O[0][2 * j], O[0][2 * j + 1], f, (uint32_t)(j | (h << (K - 1))), has_ph);
         }
-        if constexpr (STATS) {
 #pragma unroll
-            for (int j = 0; j < HX; ++j) stats_acc_f(sv, O[0][2 * j], O[0][2 * j + 1]);
-        }
+        for (int j = 0; j < HX; ++j) stats_acc_f(sv, O[0][2 * j], O[0][2 * j + 1]);
         T::store(psi, base, hoff, g, O);
         base[0] = basen[0];
         unscale = split(Bn[0], xh, xl);
         tile += stride;
     } while (tile < ntiles);
-    if constexpr (STATS) block_reduce_store(sv, 3, 0u, part + blockIdx.x * 8);
+    block_reduce_store(sv, 3, 0u, part + blockIdx.x * 8);
 }
 
 // A column's diagonal-epilogue factor (col_factor), split for a wave that
@@ -731,15 +898,6 @@ __device__ __forceinline__ ColFactor<float> epi_combine(uint32_t tb, double tr, 
     f.cr = (float)(tr * lr - ti * li);
     f.ci = (float)(tr * li + ti * lr);
     return f;
-}
-
-// Swap a (in the odd 16-lane rows of the wave) with b (in the even rows):
-// afterwards lane l of an even row holds in b what lane l + 16 held in a, and
-// lane l + 16 holds in a what lane l held in b.
-__device__ __forceinline__ void lane_swap16(float& a, float& b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
 }
 
 // ------------------------------------------------------------ cluster: float state, k = 7, fp16 matrix cores
@@ -1025,9 +1183,75 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
 // v_mfma_f64_16x16x4_f64: lane l: p = l%16 (column), q = l/16 owns target
 // indices x = j | q << (K-2), j < 2^(K-2), of its column(s). Operand A/B: lane
 // l holds row / column l%16 at inner index l/16; result register r of lane l
-// holds row 4 r + l/16, column l%16. Same prefetching loop as the float kernel.
+// holds row 4 r + l/16, column l%16.
+//
+// k = 3..5: one wave tile of 16 NB columns per wave, work-groups in memory order.
+// k = 5 keeps the fp64 matrix cores busy for two thirds of the pass, so its
+// tiles are narrow (NB = 1) and four waves share a SIMD.
+template <int K, int NB, bool NT>
+__global__ __launch_bounds__(256, NB == 1 ? 4 : 2) void k_cluster_f64_mfma(vd2* __restrict__ psi, const double* __restrict__ Ap,
+                                                             const EpiDesc* __restrict__ epi, ClusterGeom g) {
+    constexpr int D = 1 << K, HX = D / 4, RB = 2 * D / 16, S = 2 * D / 4, COLS = 16 * NB;
+    __shared__ double As[RB * S * 64];
+    const int lane = threadIdx.x & 63, p = lane & 15, q = lane >> 4;
+    const uint64_t qoff = ((q & 1) ? (uint64_t(1) << g.t[K - 2]) : 0) | ((q & 2) ? (uint64_t(1) << g.t[K - 1]) : 0);
+    const uint64_t tile = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const bool act = tile < g.ncols / COLS;
+    uint64_t base[NB];
+    double B[NB][2 * HX];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) base[nb] = deposit_cols<K>(tile * COLS + p + 16 * nb, g);
+    MatrixRegs<RB * S * 64 * 8, 256> mr(Ap);
+    if (act) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int j = 0; j < HX; ++j) {
+                const vd2 v = load16<NT>(psi + (base[nb] | qoff | target_off<K - 2>(j, g)));
+                B[nb][2 * j] = v.x;
+                B[nb][2 * j + 1] = v.y;
+            }
+    }
+    mr.store(As);
+    __syncthreads();
+    if (!act) return;
+    doublex4 acc[NB][RB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[nb][rb][i] = 0.0;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const double a = As[(rb * S + s) * 64 + lane];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[nb][rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, B[nb][s], acc[nb][rb], 0, 0, 0);
+        }
+    }
+    // acc[nb][j / 2][2 (j % 2) + {0, 1}] is output amplitude j of the lane
+    const bool has_epi = epi != nullptr, has_ph = has_epi && epi->n_ph > 0;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        ColFactor<double> f{0u, 0u, 1.0, 0.0};
+        if (has_epi) f = col_factor<double>((c_epi*)epi, base[nb]);
+#pragma unroll
+        for (int j = 0; j < HX; ++j) {
+            double re = acc[nb][j / 2][2 * (j % 2)], im = acc[nb][j / 2][2 * (j % 2) + 1];
+            if (has_epi) apply_factor(re, im, f, (uint32_t)(j | (q << (K - 2))), has_ph);
+            store16<NT>(psi + (base[nb] | qoff | target_off<K - 2>(j, g)), vd2{re, im});
+        }
+    }
+}
+
+// k = 6 (bound by the fp64 matrix cores; its matrix fills the LDS):
+// persistent, each wave prefetches its next tile of 16 columns before the
+// current tile's MFMA chain.
 template <int K, int NB, int THREADS>
-__global__ __launch_bounds__(THREADS, 512 / THREADS) void k_cluster_f64_mfma(double2* __restrict__ psi,
+__global__ __launch_bounds__(THREADS, 512 / THREADS) void k_cluster_f64_mfma_loop(double2* __restrict__ psi,
                                                                            const double* __restrict__ Ap,
                                                                            const EpiDesc* __restrict__ epi,
                                                                            ClusterGeom g) {
@@ -1357,20 +1581,48 @@ __global__ __launch_bounds__(256, 2) void k_cluster_f32_stage(float2* __restrict
                                  g.ncols >> C, (uint64_t)gridDim.x * 4);
 }
 
-template <int K, int C>
-struct StageF64 {
-    static constexpr int HX = (1 << K) / 4;
-    static constexpr int NB = (1 << C) / 16;
-    static constexpr int NL = (1 << (K + C)) / 64;
-    // t0: the tile's base (uniform in the wave); lane_off: the lane's bits
-    __device__ __forceinline__ static void load_lin(const vd2* __restrict__ psi, uint64_t t0, uint64_t lane_off,
-                                                    const StageGeom& sg, vd2 (&R)[NL]) {
+// double: lane l covers tau = i * 64 + l in linear order; in MFMA order lane
+// (p, q) owns target indices j | q << (K-2) of columns p and p + 16. One wave
+// tile per wave, work-groups in memory order. The 32 KiB matrix of k = 5 takes
+// the place of the four tiles in LDS once they are in registers (as in
+// k_cluster_f32_split6s); its tiles have 16 columns (C = 4), so four
+// work-groups share a compute unit and the fp64 products (two thirds of the
+// pass) run under the others' accesses. k = 5, 28 qubits, 23 target sets: 1.60
+// ms against 1.68 ms as a persistent grid of 8-wave work-groups and 1.78 ms for
+// the direct kernel; 24 qubits 98 us against 143 us. k = 3 / 4: 1.52 / 1.60
+// against 1.68 / 1.70 ms.
+template <int K, int C, bool NT>
+__global__ __launch_bounds__(256, C == 4 ? 4 : 2) void k_cluster_f64_stage(vd2* __restrict__ psi, const double* __restrict__ Ap,
+                                                              const EpiDesc* __restrict__ epi, ClusterGeom g,
+                                                              StageGeom sg) {
+    constexpr int D = 1 << K, HX = D / 4, RB = 2 * D / 16, S = 2 * D / 4, NB = (1 << C) / 16, TB = K + C,
+                  TILE = 1 << TB, NL = TILE / 64, AN = RB * S * 64;
+    constexpr bool SHARE = K == 5;
+    __shared__ vd2 Ls[4 * TILE + (SHARE ? 0 : AN / 2)];
+    static_assert(!SHARE || AN / 2 <= 4 * TILE, "the matrix fits the tiles' place");
+    double* As = reinterpret_cast<double*>(SHARE ? Ls : Ls + 4 * TILE);
+    const int lane = threadIdx.x & 63, p = lane & 15, q = lane >> 4,
+              w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: the tile base is scalar
+    vd2* L = Ls + w * TILE;
+    uint64_t lane_off = 0;
 #pragma unroll
-        for (int i = 0; i < NL; ++i) R[i] = *reinterpret_cast<const vd2*>(psi + ((t0 | sg.ioff[i]) | lane_off));
+    for (int b = 0; b < 6; ++b)
+        if ((lane >> b) & 1) lane_off |= uint64_t(1) << sg.tb[b];
+    const uint64_t tile = (uint64_t)blockIdx.x * 4 + w;
+    const bool act = tile < (g.ncols >> C);
+    const uint64_t tb0 = tile_base<TB>(tile, sg);
+    vd2 R[NL];
+    if (act) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) R[i] = load16<NT>(psi + ((tb0 | sg.ioff[i]) | lane_off));
     }
-    __device__ __forceinline__ static void stage_in(vd2* L, int lane, const int (&tc)[NB], int tq,
-                                                    const StageGeom& sg, const vd2 (&R)[NL],
-                                                    double (&B)[NB][2 * HX]) {
+    MatrixRegs<AN * 8, 256> mr(Ap);
+    int tc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) tc[nb] = tau_of_column<C>(p + 16 * nb, sg);
+    const int tq = ((q & 1) << sg.tpos[K - 2]) | ((q >> 1) << sg.tpos[K - 1]);
+    double B[NB][2 * HX];
+    if (act) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) L[i * 64 + lane] = R[i];
         wave_lds_fence();
@@ -1382,105 +1634,44 @@ struct StageF64 {
                 B[nb][2 * j] = v.x;
                 B[nb][2 * j + 1] = v.y;
             }
-        wave_lds_fence();
     }
-};
-
-// double: lane l covers tau = i * 64 + l in linear order; in MFMA order lane
-// (p, q) owns target indices j | q << (K-2) of columns p and p + 16.
-template <int K, int C, int THREADS>
-__global__ __launch_bounds__(THREADS, 512 / THREADS) void k_cluster_f64_stage(vd2* __restrict__ psi,
-                                                                            const double* __restrict__ Ap,
-                                                                            const EpiDesc* __restrict__ epi,
-                                                                            ClusterGeom g, StageGeom sg) {
-    constexpr int D = 1 << K;
-    constexpr int HX = D / 4;
-    constexpr int RB = 2 * D / 16;
-    constexpr int S = 2 * D / 4;
-    constexpr int NB = (1 << C) / 16;
-    constexpr int NT = K + C;
-    constexpr int TILE = 1 << NT;
-    constexpr int NL = TILE / 64;
-    constexpr int WAVES = THREADS / 64;
-    __shared__ double As[RB * S * 64];
-    __shared__ vd2 Ls[WAVES][TILE];
-    load_matrix<RB * S * 64, THREADS>(As, reinterpret_cast<const vf4*>(Ap));
+    if constexpr (SHARE) __syncthreads();
+    mr.store(As);
     __syncthreads();
-
-    const int lane = threadIdx.x & 63, p = lane & 15, q = lane >> 4,
-              w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: tile bases are scalar
-    vd2* L = Ls[w];
-    uint64_t lane_off = 0;
+    doublex4 acc[NB][RB];
 #pragma unroll
-    for (int b = 0; b < 6; ++b)
-        if ((lane >> b) & 1) lane_off |= uint64_t(1) << sg.tb[b];
-    int tc[NB];
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) tc[nb] = tau_of_column<C>(p + 16 * nb, sg);
-    const int tq = ((q & 1) << sg.tpos[K - 2]) | ((q >> 1) << sg.tpos[K - 1]);
-    const uint64_t ntiles = g.ncols >> C;
-    const uint64_t stride = (uint64_t)gridDim.x * WAVES;
-    const bool has_epi = epi != nullptr;
-    const bool has_ph = has_epi && epi->n_ph > 0;
-
-    uint64_t tile = (uint64_t)xcd_block() * WAVES + w;
-    if (tile >= ntiles) return;
-    const uint64_t last = ntiles - 1;
-    vd2 R[NL];
-    StageF64<K, C>::load_lin(psi, tile_base<NT>(tile, sg), lane_off, sg, R);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_sched_barrier(0);
-    double B[NB][2 * HX];
-    StageF64<K, C>::stage_in(L, lane, tc, tq, sg, R, B);
-    do {
-        asm volatile("" : "+v"(lane_off));  // chunk addresses recomputed, not held across the loop
-        const uint64_t nxt = tile + stride < last ? tile + stride : last;
-        StageF64<K, C>::load_lin(psi, tile_base<NT>(nxt, sg), lane_off, sg, R);
-        __builtin_amdgcn_sched_barrier(0);
-
-        doublex4 acc[NB][RB];
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+            for (int i = 0; i < 4; ++i) acc[nb][rb][i] = 0.0;
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
+    for (int s = 0; s < S; ++s) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[nb][rb][i] = 0.0;
-        int aoff = lane;
-        asm volatile("" : "+v"(aoff));
+        for (int rb = 0; rb < RB; ++rb) {
+            const double a = As[(rb * S + s) * 64 + lane];
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                const double a = As[(rb * S + s) * 64 + aoff];
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    acc[nb][rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, B[nb][s], acc[nb][rb], 0, 0, 0);
-            }
+            for (int nb = 0; nb < NB; ++nb)
+                acc[nb][rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, B[nb][s], acc[nb][rb], 0, 0, 0);
         }
-        const uint64_t tb0 = tile_base<NT>(tile, sg);
+    }
+    if constexpr (SHARE) __syncthreads();  // every wave is done with the matrix
+    if (!act) return;
+    const bool has_epi = epi != nullptr, has_ph = has_epi && epi->n_ph > 0;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            ColFactor<double> f{0u, 0u, 1.0, 0.0};
-            // the column's state bits are rebuilt here (a few scalar-indexed
-            // ORs) rather than held across the loop, where they were spilled
-            if (has_epi) f = col_factor<double>(epi, tb0 | state_bits_of_column<C>(p + 16 * nb, sg));
+    for (int nb = 0; nb < NB; ++nb) {
+        ColFactor<double> f{0u, 0u, 1.0, 0.0};
+        if (has_epi) f = col_factor<double>((c_epi*)epi, tb0 | state_bits_of_column<C>(p + 16 * nb, sg));
 #pragma unroll
-            for (int j = 0; j < HX; ++j) {
-                double re = acc[nb][j / 2][2 * (j % 2)], im = acc[nb][j / 2][2 * (j % 2) + 1];
-                if (has_epi) apply_factor(re, im, f, (uint32_t)(j | (q << (K - 2))), has_ph);
-                L[tc[nb] | tq | tau_of_targets<0, K - 2>(j, sg)] = vd2{re, im};
-            }
+        for (int j = 0; j < HX; ++j) {
+            double re = acc[nb][j / 2][2 * (j % 2)], im = acc[nb][j / 2][2 * (j % 2) + 1];
+            if (has_epi) apply_factor(re, im, f, (uint32_t)(j | (q << (K - 2))), has_ph);
+            L[tc[nb] | tq | tau_of_targets<0, K - 2>(j, sg)] = vd2{re, im};
         }
-        wave_lds_fence();
-        {
+    }
+    wave_lds_fence();
 #pragma unroll
-            for (int i = 0; i < NL; ++i) *reinterpret_cast<vd2*>(psi + ((tb0 | sg.ioff[i]) | lane_off)) = L[i * 64 + lane];
-        }
-        wave_lds_fence();
-        StageF64<K, C>::stage_in(L, lane, tc, tq, sg, R, B);
-        tile += stride;
-    } while (tile < ntiles);
+    for (int i = 0; i < NL; ++i) store16<NT>(psi + ((tb0 | sg.ioff[i]) | lane_off), (vd2)L[i * 64 + lane]);
 }
 
 // ------------------------------------------------------------ several 5-qubit clusters per pass
@@ -2125,23 +2316,126 @@ __device__ __forceinline__ void split6s_tiles(g_float2* __restrict__ gpsi, const
     } while (tile < tile_end);
 }
 
-template <bool LOWT>
-__global__ __launch_bounds__(512, 1) void k_cluster_f32_split6s(float2* __restrict__ psi,
+// Staged 6-qubit kernel: one wave tile per wave, work-groups in memory order
+// (see k_cluster_f32_split6). The work-group's 64 KiB of LDS hold its four
+// tiles first (linear loads, each lane reads its column), then the matrix,
+// then the results on their way to linear stores: two work-groups per compute
+// unit, so one's loads and stores run under the other's product. Its tile is
+// read in whole lines whatever the targets are: 30 qubits, 23 target sets, mean
+// 3.08 ms (worst 3.7) against 3.52 ms as a persistent grid that held the matrix
+// and half tiles side by side.
+template <bool LOWT, bool NT>
+__global__ __launch_bounds__(256, 2) void k_cluster_f32_split6s(float2* __restrict__ psi,
                                                                 const half8* __restrict__ Ap,
                                                                 const EpiDesc* __restrict__ epi, StageGeom sg,
                                                                 uint64_t ntiles) {
-    constexpr int RB = 4, S = 8, WAVES = 8;
-    __shared__ half8 Ah[RB * S * 64];
-    __shared__ half8 Al[RB * S * 64];
-    __shared__ float2 Ls[WAVES][1024];
-    load_matrix<RB * S * 64 * 8, WAVES * 64>(reinterpret_cast<_Float16*>(Ah), reinterpret_cast<const vf4*>(Ap));
-    load_matrix<RB * S * 64 * 8, WAVES * 64>(reinterpret_cast<_Float16*>(Al),
-                                            reinterpret_cast<const vf4*>(Ap + RB * S * 64));
-    __syncthreads();
-    // the wave index is uniform in the wave: tile numbers and bases are scalar
+    constexpr int K = 6, C = 5, TB = K + C, HX = 32, RB = 4, S = 8, NL = 16, NP = RB * S * 64;
+    __shared__ half8 L[2 * NP];
+    const int lane = threadIdx.x & 63, p = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    split6s_tiles<LOWT>((g_float2*)psi, Ah, Al, Ls[w], (c_epi*)epi, sg, (uint64_t)xcd_block() * WAVES + w, ntiles,
-                        (uint64_t)gridDim.x * WAVES);
+    const uint64_t tile = (uint64_t)blockIdx.x * 4 + w;
+    const bool act = tile < ntiles;
+    vf4* T4 = reinterpret_cast<vf4*>(L) + w * 1024;  // this wave's tile
+    constexpr bool PAIR = !LOWT;
+    const int cpair = PAIR ? 2 * (p & 15) : p, cown = PAIR ? (p >> 4) & 1 : 0;
+    auto sslot = [&](int v) {  // LDS slot of tau (the geometry's swizzle; linear over XOR)
+        int o = v;
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            if ((v >> (5 + i)) & 1) o ^= sg.swz[i];
+        return o;
+    };
+    const int lin = sslot(2 * lane);
+    const int lslot = sslot(tau_of_column<C>(cpair, sg) | (h << sg.tpos[K - 1]) | (cown << sg.tpos[0]));
+    int cmask[4], rmask[K - 1];
+    uint64_t imask[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        cmask[b] = sslot(128 << b);
+        imask[b] = uint64_t(1) << sg.tb[7 + b];
+    }
+#pragma unroll
+    for (int m = 0; m < K - 1; ++m) rmask[m] = sslot(1 << sg.tpos[m]);
+    auto sel = [](int i, auto& m, auto o, int nb) {
+#pragma unroll
+        for (int b = 0; b < 5; ++b)
+            if (b < nb && ((i >> b) & 1)) o ^= m[b];
+        return o;
+    };
+    uint64_t lane_off = 0;  // state offset of tile bits 1..6 (the lane of a linear access)
+#pragma unroll
+    for (int b = 0; b < 6; ++b)
+        if ((lane >> b) & 1) lane_off |= uint64_t(1) << sg.tb[b + 1];
+    const uint64_t tb0 = tile_base<TB>(tile, sg);
+    vf4* mem = reinterpret_cast<vf4*>(psi + (tb0 | lane_off));
+    vf4 R[NL];
+    if (act) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) R[i] = load16<NT>(mem + (sel(i, imask, uint64_t(0), 4) >> 1));
+    }
+    MatrixRegs<2 * NP * 16, 256> mr(Ap);
+    float X[2 * HX];
+    if (act) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) T4[sel(i, cmask, lin, 4) >> 1] = R[i];
+        wave_lds_fence();
+#pragma unroll
+        for (int j = 0; j < HX; j += 2) {
+            const vf4 v = T4[sel(PAIR ? j & ~1 : j, rmask, lslot, 5) >> 1];
+            X[2 * j] = v.x; X[2 * j + 1] = v.y; X[2 * j + 2] = v.z; X[2 * j + 3] = v.w;
+        }
+    }
+    __syncthreads();
+    mr.store(L);
+    if constexpr (PAIR) {  // rows j, j + 1 of the lane's own column
+#pragma unroll
+        for (int j = 0; j < HX; j += 2) {
+            lane_swap16(X[2 * j], X[2 * j + 2]);
+            lane_swap16(X[2 * j + 1], X[2 * j + 3]);
+        }
+    }
+    half8 xh[S], xl[S];
+    const float unscale = __builtin_ldexpf(1.0f, -split_halves<2 * HX>(X, xh, xl) - 4);
+    __syncthreads();
+    floatx16 acc[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[rb][i] = 0.0f;
+#pragma unroll
+    for (int st = 0; st < S; ++st) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const half8 ah = L[(rb * S + st) * 64 + lane];
+            const half8 al = L[NP + (rb * S + st) * 64 + lane];
+            acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, xl[st], acc[rb], 0, 0, 0);
+            acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, xh[st], acc[rb], 0, 0, 0);
+            acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, xh[st], acc[rb], 0, 0, 0);
+        }
+    }
+    __syncthreads();  // every wave is done with the matrix
+    if (!act) return;
+#pragma unroll
+    for (int j = 0; j < 2 * HX; ++j) X[j] = acc[j / 16][j % 16] * unscale;
+    if (epi != nullptr) {
+        const ColFactor<float> f = col_factor<float>((c_epi*)epi, tb0 | state_bits_of_column<C>(cpair | cown, sg));
+        const bool has_ph = epi->n_ph > 0;
+#pragma unroll
+        for (int j = 0; j < HX; ++j)
+            apply_factor(X[2 * j], X[2 * j + 1], f, (uint32_t)(j | (h << (K - 1))), has_ph);
+    }
+#pragma unroll
+    for (int j = 0; j < HX; j += 2) {
+        if constexpr (PAIR) {
+            lane_swap16(X[2 * j], X[2 * j + 2]);
+            lane_swap16(X[2 * j + 1], X[2 * j + 3]);
+        }
+        T4[sel(j, rmask, lslot, 5) >> 1] = vf4{X[2 * j], X[2 * j + 1], X[2 * j + 2], X[2 * j + 3]};
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+        store16<NT>(mem + (sel(i, imask, uint64_t(0), 4) >> 1), (vf4)T4[sel(i, cmask, lin, 4) >> 1]);
 }
 
 // ------------------------------------------------------------ uniform start + two clusters, one write-only pass
@@ -2668,7 +2962,16 @@ __global__ __launch_bounds__(256) void k_cluster_valu(typename Cplx<T>::type* __
     }
 }
 
-// Two- and three-qubit clusters. With one column per thread, targets among
+// (ar, ai) += m v, in one fixed contraction: the forms of a cluster kernel
+// with and without the sums store the same bits.
+template <typename T, typename M, typename V>
+__device__ __forceinline__ void cmac(T& ar, T& ai, const M& m, const V& v) {
+    ar += __builtin_elementwise_fma(m.x, v.x, -(m.y * v.y));
+    ai += __builtin_elementwise_fma(m.x, v.y, m.y * v.x);
+}
+
+// Two- and three-qubit clusters on states that fit the caches, and (STATS) a last
+// one whose sums are wanted. With one column per thread, targets among
 // the lowest state bits put lanes 2^k amplitudes apart, so each load
 // instruction spreads over 2^k times the cache lines it uses, and a thread
 // that holds its column and the matrix limits occupancy. Here a wave tile is
@@ -2678,11 +2981,11 @@ __global__ __launch_bounds__(256) void k_cluster_valu(typename Cplx<T>::type* __
 // column, then takes the results back for contiguous stores. STATS (float
 // only): also sum p, p^2 and -p ln p of the stored amplitudes into part (per
 // work-group), as the matrix-core kernels' STATS forms do.
-template <typename T, int K, bool STATS = false>
-__global__ __launch_bounds__(256) void k_cluster_valu_staged(typename Cplx<T>::type* __restrict__ psi,
-                                                             const typename Cplx<T>::type* __restrict__ M,
-                                                             const EpiDesc* __restrict__ epi, StageGeom sg,
-                                                             uint64_t tiles, double* __restrict__ part) {
+template <typename T, int K, bool STATS>
+__device__ __forceinline__ void valu_columns(typename Cplx<T>::type* __restrict__ psi,
+                                             const typename Cplx<T>::type* __restrict__ M,
+                                             const EpiDesc* __restrict__ epi, const StageGeom& sg, uint64_t tiles,
+                                             double* __restrict__ part) {
     static_assert(!STATS || std::is_same<T, float>::value, "sums of float states only");
     using V = typename Cplx<T>::type;
     constexpr int D = 1 << K, RS = D + 1;  // LDS row of a column, padded
@@ -2737,9 +3040,7 @@ __global__ __launch_bounds__(256) void k_cluster_valu_staged(typename Cplx<T>::t
             T ar = 0, ai = 0;
 #pragma unroll
             for (int x = 0; x < D; ++x) {
-                const V m = Ms[y * D + x];
-                ar += m.x * v[x].x - m.y * v[x].y;
-                ai += m.x * v[x].y + m.y * v[x].x;
+                cmac(ar, ai, Ms[y * D + x], v[x]);
             }
             if (has_epi) apply_factor(ar, ai, f, (uint32_t)y, has_ph);
             if constexpr (STATS) stats_acc_f(sv, ar, ai);
@@ -2756,179 +3057,397 @@ __global__ __launch_bounds__(256) void k_cluster_valu_staged(typename Cplx<T>::t
     if constexpr (STATS) block_reduce_store(sv, 3, 0u, part + blockIdx.x * 8);  // every thread gets here
 }
 
-// ------------------------------------------------------------ diagonal pass
-// Every amplitude times the diagonal factor of its index (Sec. 3.5: diagonal
-// gates need no gather). A wave covers windows of 128 consecutive amplitudes
-// (2 per lane, 16-byte accesses), U neighbouring windows per step, all loaded
-// before any factor is applied. The index splits into lo (bits 0..6, fixed per
-// lane) and hi (the window, uniform per wave): terms of lo bits only are
-// per-lane constants; CZ pairs with one bit in each half give a sign mask over
-// lo. The hi part (sign, mask and phase) costs a loop over every gate of the
-// pass, too much per window, so a wave takes runs of 64 windows: each lane
-// forms the hi part of one window of the run and the window reads it from that
-// lane. The descriptor lists the pairs in `cc` and the phases in `ph`.
-template <typename T>
-__device__ __forceinline__ void load_pair(const typename Cplx<T>::type* p, typename Cplx<T>::type (&v)[2]) {
-    v[0] = p[0];
-    v[1] = p[1];
-}
-template <>
-__device__ __forceinline__ void load_pair<float>(const float2* p, float2 (&v)[2]) {
-    const float4 w = *reinterpret_cast<const float4*>(p);  // p is 16-byte aligned (even index)
-    v[0] = make_float2(w.x, w.y);
-    v[1] = make_float2(w.z, w.w);
-}
-template <typename T>
-__device__ __forceinline__ void store_pair(typename Cplx<T>::type* p, const typename Cplx<T>::type (&v)[2]) {
-    p[0] = v[0];
-    p[1] = v[1];
-}
-template <>
-__device__ __forceinline__ void store_pair<float>(float2* p, const float2 (&v)[2]) {
-    *reinterpret_cast<float4*>(p) = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
+template <typename T, int K>
+__global__ __launch_bounds__(256) void k_cluster_valu_cached(typename Cplx<T>::type* __restrict__ psi,
+                                                             const typename Cplx<T>::type* __restrict__ M,
+                                                             const EpiDesc* __restrict__ epi, StageGeom sg,
+                                                             uint64_t tiles) {
+    valu_columns<T, K, false>(psi, M, epi, sg, tiles, nullptr);
 }
 
-template <typename T, int U>
-__global__ __launch_bounds__(256) void k_diag(typename Cplx<T>::type* __restrict__ psi, int n,
-                                              const EpiDesc* __restrict__ e) {
+// Clusters of one to three qubits on states beyond the caches: 8 KiB
+// of state per wave (the targets and the lowest other bits), one tile per
+// wave, work-groups in memory order. The tile moves as linear 16-byte accesses
+// of whole runs whatever the targets are, all in flight at once; LDS hands
+// each lane its columns and takes the results back. 28 qubits complex64, k = 1 /
+// 2 / 3: 755 / 768 / 747 us against 862 / 845 / 832 us for the kernels above,
+// which win inside the caches (18 qubits: 6.2 against 9.2 us for k = 1: more
+// waves, each with less to do).
+template <typename T, int K>
+__device__ __forceinline__ void valu_tile(typename Cplx<T>::type* __restrict__ psi,
+                                          const typename Cplx<T>::type* __restrict__ M,
+                                          const EpiDesc* __restrict__ epi, const StageGeom& sg, uint64_t tiles) {
     using V = typename Cplx<T>::type;
-    constexpr int LO = 7;         // amplitude index bits inside a window
-    constexpr int RB = 6;         // a wave takes runs of 2^RB windows, one per lane
-    constexpr int R = 1 << RB;
-    const int lane = threadIdx.x & 63;
-    const int np = e->n_cc, nph = e->n_ph;
-    // per-lane constants: the factor of the two lo indices of this lane
-    uint32_t sgn_lo[2] = {0u, 0u};
-    double plr[2] = {1.0, 1.0}, pli[2] = {0.0, 0.0};
+    constexpr bool F = sizeof(T) == 4;
+    constexpr int D = 1 << K, TB = F ? 10 : 9, C = TB - K, NC = (1 << C) / 64;  // columns of a lane: lane + 64 i
+    constexpr int AB = F ? 1 : 0;  // tau bits of one 16-byte access
+    typedef T vt2 __attribute__((ext_vector_type(2)));
+    __shared__ V Ms[D * D];
+    __shared__ vf4 Ls[4][512];
+    if ((int)threadIdx.x < D * D) Ms[threadIdx.x] = M[threadIdx.x];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    vf4* L4 = Ls[w];
+    vt2* L = reinterpret_cast<vt2*>(L4);
+    const uint64_t tile = (uint64_t)blockIdx.x * 4 + w;
+    const bool act = tile < tiles;
+    const uint64_t tb0 = tile_base<TB>(tile, sg);
+    // slot of tau: its upper bits folded into the bank bits (linear over XOR)
+    auto slot = [](int t) { return F ? t ^ (((t >> 5) & 15) << 1) : t ^ ((t >> 4) & 15); };
+    uint64_t lane_off = 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const uint32_t lo = 2 * lane + h;
-        for (int i = 0; i < np; ++i) {
-            const int a = e->cc[i][0], b = e->cc[i][1];
-            if (a < LO && b < LO) sgn_lo[h] ^= (lo >> a) & (lo >> b) & 1u;
-        }
-        for (int i = 0; i < nph; ++i) {
-            const int q = e->ph_q[i];
-            if (q < LO && ((lo >> q) & 1u)) {
-                const double c = e->ph[i][0], sn = e->ph[i][1];
-                const double r = plr[h] * c - pli[h] * sn;
-                pli[h] = plr[h] * sn + pli[h] * c;
-                plr[h] = r;
+    for (int b = 0; b < 6; ++b)
+        if ((lane >> b) & 1) lane_off |= uint64_t(1) << sg.tb[b + AB];
+    auto at = [&](int i) -> vf4* {  // linear access i of the tile
+        return reinterpret_cast<vf4*>(psi + ((tb0 | sg.ioff[i]) | lane_off));
+    };
+    if (act) {
+        vf4 R[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) R[i] = load16<true>((const vf4*)at(i));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) L4[slot((i * 64 + lane) << AB) >> AB] = R[i];
+    }
+    __syncthreads();
+    if (!act) return;
+    const bool has_epi = epi != nullptr, has_ph = has_epi && epi->n_ph > 0;
+    int rs[D];
+#pragma unroll
+    for (int x = 0; x < D; ++x) rs[x] = slot(tau_of_targets<0, K>(x, sg));
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        int tc = 0;
+        uint64_t cb = 0;
+#pragma unroll
+        for (int b = 0; b < C; ++b)
+            if (((lane + 64 * i) >> b) & 1) {
+                tc |= 1 << sg.cpos[b];
+                cb |= uint64_t(1) << sg.tb[sg.cpos[b]];
             }
+        const int ts = slot(tc);
+        vt2 v[D];
+#pragma unroll
+        for (int x = 0; x < D; ++x) v[x] = L[ts ^ rs[x]];
+        ColFactor<T> f{0u, 0u, T(1), T(0)};
+        if (has_epi) f = col_factor<T>((c_epi*)epi, tb0 | cb);
+#pragma unroll
+        for (int y = 0; y < D; ++y) {
+            T ar = 0, ai = 0;
+#pragma unroll
+            for (int x = 0; x < D; ++x) {
+                cmac(ar, ai, Ms[y * D + x], v[x]);
+            }
+            if (has_epi) apply_factor(ar, ai, f, (uint32_t)y, has_ph);
+            L[ts ^ rs[y]] = vt2{ar, ai};  // the column's own slots
         }
     }
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) store16<true>(at(i), (vf4)L4[slot((i * 64 + lane) << AB) >> AB]);
+}
+
+// STATS: the persistent form, since the partials of one work-group per tile
+// would outgrow their area.
+template <typename T, int K, bool STATS = false>
+__global__ __launch_bounds__(256, sizeof(T) == 4 && K == 3 ? 3 : 4) void k_cluster_valu_staged(
+    typename Cplx<T>::type* __restrict__ psi, const typename Cplx<T>::type* __restrict__ M,
+    const EpiDesc* __restrict__ epi, StageGeom sg, uint64_t tiles, double* __restrict__ part) {
+    if constexpr (STATS)
+        valu_columns<T, K, true>(psi, M, epi, sg, tiles, part);
+    else
+        valu_tile<T, K>(psi, M, epi, sg, tiles);
+}
+
+// ------------------------------------------------------------ diagonal pass
+// Every amplitude times the diagonal factor of its index (Sec. 3.5: diagonal
+// gates need no gather). A work-group covers a run of 64 windows of 128
+// consecutive amplitudes, 16 per wave, loaded up to 16 at a time before any
+// factor is applied. The index splits into lo (bits 0..6, fixed per lane) and
+// hi (the window, uniform per wave): terms of lo bits only are per-lane
+// constants; CZ pairs with one bit in each half give a sign mask over lo. Both
+// parts cost a loop over every gate of the pass, so the work-group forms them
+// once: wave w takes every fourth gate, lane j the lo part of its own two
+// indices and the hi part of window j of the run, and LDS combines the four
+// waves' parts. 28 qubits complex64, 14 pairs and 10 phases: 690 us (6.2 TB/s)
+// against 835 us for a wave that walked runs of its own; 20 qubits: 18 against
+// 35 us, where those loops are most of it. Each XCD takes its own stretch here
+// (linear accesses: 690 us against 734 us in plain order). The descriptor lists the pairs in `cc` and the phases in `ph`.
+template <typename T, bool NT>
+__global__ __launch_bounds__(256) void k_diag(typename Cplx<T>::type* __restrict__ psi, int n,
+                                              const EpiDesc* __restrict__ desc) {
+    constexpr bool F = sizeof(T) == 4;
+    constexpr int LO = 7;                 // amplitude index bits inside a window
+    constexpr int RB = 6;                 // a work-group's run: 2^RB windows
+    constexpr int W = (1 << RB) / 4;      // windows of a wave
+    constexpr int U = F ? 16 : 8;         // of them in flight at a time
+    c_epi* e = (c_epi*)desc;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t run = xcd_block();
     const uint64_t N = uint64_t(1) << n;
-    const uint64_t nwin = (n >= LO) ? (uint64_t(1) << (n - LO)) : 1;
-    const uint64_t nrun = (nwin + R - 1) >> RB;
-    const uint64_t rstride = (uint64_t)gridDim.x * 4;
-    for (uint64_t run = (uint64_t)xcd_block() * 4 + (threadIdx.x >> 6); run < nrun; run += rstride) {
-        // lane j forms the hi part of the factor of window j of the run: the
-        // sign of CZ pairs on hi bits, the sign mask over lo of pairs with
-        // one bit in each half, and the phases of hi bits
-        const uint64_t hi = ((run << RB) | (uint64_t)lane) << LO;
-        uint32_t sgn_hi = 0u, wmask = 0u;
-        double phr = 1.0, phi = 0.0;
-        for (int i = 0; i < np; ++i) {
+    const uint64_t nwin = n >= LO ? uint64_t(1) << (n - LO) : 1;
+    // this wave's share of the gates: signs of the lane's two lo indices (bits
+    // 0, 1), sign mask over lo (bits 2..8) and sign (bit 9) of window `lane`,
+    // phases of the two lo indices and of the window
+    __shared__ uint32_t Ps[4][64];
+    __shared__ double Pr[4][3][64], Pi[4][3][64];
+    const uint64_t hi = ((run << RB) | (uint64_t)lane) << LO;
+    {
+        uint32_t sg = 0u, wm = 0u, sh = 0u;
+        double r[3] = {1.0, 1.0, 1.0}, q[3] = {0.0, 0.0, 0.0};
+        const int np = e->n_cc, nph = e->n_ph;
+        for (int i = w; i < np; i += 4) {
             const int a = e->cc[i][0], b = e->cc[i][1];
-            if (a >= LO && b >= LO) sgn_hi ^= (uint32_t)((hi >> a) & (hi >> b) & 1);
-            else if (a < LO && b >= LO) wmask ^= (uint32_t)((hi >> b) & 1) << a;
-            else if (b < LO && a >= LO) wmask ^= (uint32_t)((hi >> a) & 1) << b;
-        }
-        for (int i = 0; i < nph; ++i) {
-            const int q = e->ph_q[i];
-            if (q >= LO && ((hi >> q) & 1)) {
-                const double c = e->ph[i][0], sn = e->ph[i][1];
-                const double r = phr * c - phi * sn;
-                phi = phr * sn + phi * c;
-                phr = r;
+            if (a < LO && b < LO) {
+                const uint32_t l0 = 2 * lane, l1 = l0 + 1;
+                sg ^= ((l0 >> a) & (l0 >> b) & 1u) | (((l1 >> a) & (l1 >> b) & 1u) << 1);
+            } else if (a >= LO && b >= LO) {
+                sh ^= (uint32_t)((hi >> a) & (hi >> b) & 1);
+            } else if (a < LO) {
+                wm ^= (uint32_t)((hi >> b) & 1) << a;
+            } else {
+                wm ^= (uint32_t)((hi >> a) & 1) << b;
             }
         }
-        const int sw = (int)(wmask | (sgn_hi << LO));  // wmask has bits 0..6 only
-        const uint64_t left = nwin - (run << RB);
-        const int wend = left < (uint64_t)R ? (int)left : R;  // uniform
-        for (int w0 = 0; w0 < wend; w0 += U) {
-            V v[U][2];
+        for (int i = w; i < nph; i += 4) {
+            const int b = e->ph_q[i];
+            const double c = e->ph[i][0], sn = e->ph[i][1];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint64_t i0 = (((run << RB) | (uint64_t)(w0 + u)) << LO) | (uint64_t)(2 * lane);
-                // windows past the end, and lanes past the end of states of fewer than 7 qubits
-                if (w0 + u < wend && i0 < N) load_pair<T>(psi + i0, v[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint64_t i0 = (((run << RB) | (uint64_t)(w0 + u)) << LO) | (uint64_t)(2 * lane);
-                if (w0 + u >= wend || i0 >= N) continue;
-                const uint32_t swu = (uint32_t)__builtin_amdgcn_readlane(sw, w0 + u);
-                const double hr = readlane_f64(phr, w0 + u), hq = readlane_f64(phi, w0 + u);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t lo = 2 * lane + h;
-                    const bool neg = ((sgn_lo[h] ^ (swu >> LO) ^ (uint32_t)__popc(lo & swu & 0x7fu)) & 1u) != 0;
-                    const T fr = (T)(hr * plr[h] - hq * pli[h]);
-                    const T fi = (T)(hr * pli[h] + hq * plr[h]);
-                    const T re = v[u][h].x * fr - v[u][h].y * fi;
-                    const T im = v[u][h].x * fi + v[u][h].y * fr;
-                    v[u][h].x = neg ? -re : re;
-                    v[u][h].y = neg ? -im : im;
+            for (int k = 0; k < 3; ++k) {
+                const bool on = k == 2 ? b >= LO && ((hi >> b) & 1) : b < LO && (((2 * lane + k) >> b) & 1);
+                if (on) {
+                    const double t = r[k] * c - q[k] * sn;
+                    q[k] = r[k] * sn + q[k] * c;
+                    r[k] = t;
                 }
-                store_pair<T>(psi + i0, v[u]);
+            }
+        }
+        Ps[w][lane] = sg | wm << 2 | sh << 9;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            Pr[w][k][lane] = r[k];
+            Pi[w][k][lane] = q[k];
+        }
+    }
+    __syncthreads();
+    uint32_t ps = 0u;
+    double r[3] = {1.0, 1.0, 1.0}, q[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        ps ^= Ps[v][lane];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double c = Pr[v][k][lane], sn = Pi[v][k][lane];
+            const double t = r[k] * c - q[k] * sn;
+            q[k] = r[k] * sn + q[k] * c;
+            r[k] = t;
+        }
+    }
+    typedef T vt2 __attribute__((ext_vector_type(2)));
+    constexpr int PER = F ? 1 : 2;  // 16-byte accesses of a lane per window
+#pragma unroll
+    for (int w0 = 0; w0 < W; w0 += U) {
+        vf4 v[U * PER];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t win = (run << RB) | (uint64_t)(w * W + w0 + u);
+            const uint64_t i0 = (win << LO) | (uint64_t)(2 * lane);
+            // windows past the end, and lanes past the end of states of fewer than 7 qubits
+            if (win < nwin && i0 < N)
+#pragma unroll
+                for (int k = 0; k < PER; ++k) v[u * PER + k] = load16<NT>(reinterpret_cast<const vf4*>(psi + i0) + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int wl = w * W + w0 + u;
+            const uint64_t win = (run << RB) | (uint64_t)wl;
+            const uint64_t i0 = (win << LO) | (uint64_t)(2 * lane);
+            const uint32_t pw = (uint32_t)__builtin_amdgcn_readlane((int)ps, wl) >> 2;
+            const double hr = readlane_f64(r[2], wl), hq = readlane_f64(q[2], wl);
+            if (win >= nwin || i0 >= N) continue;
+            T z[4];
+            if constexpr (F) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) z[k] = v[u][k];
+            } else {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const vt2 d = __builtin_bit_cast(vt2, v[u * PER + k]);
+                    z[2 * k] = d.x;
+                    z[2 * k + 1] = d.y;
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t lo = 2 * lane + h;
+                const bool neg = ((ps >> h ^ pw >> 7 ^ (uint32_t)__popc(lo & pw & 0x7fu)) & 1u) != 0;
+                const T fr = (T)(hr * r[h] - hq * q[h]);
+                const T fi = (T)(hr * q[h] + hq * r[h]);
+                const T re = z[2 * h] * fr - z[2 * h + 1] * fi;
+                const T im = z[2 * h] * fi + z[2 * h + 1] * fr;
+                z[2 * h] = neg ? -re : re;
+                z[2 * h + 1] = neg ? -im : im;
+            }
+            vf4* out = reinterpret_cast<vf4*>(psi + i0);
+            if constexpr (F) {
+                store16<NT>(out, vf4{z[0], z[1], z[2], z[3]});
+            } else {
+                store16<NT>(out, __builtin_bit_cast(vf4, vt2{z[0], z[1]}));
+                store16<NT>(out + 1, __builtin_bit_cast(vf4, vt2{z[2], z[3]}));
             }
         }
     }
 }
 
 // ------------------------------------------------------------ per-gate kernels
+// The plain method's kernels stream the state in 16-byte units (one complex128
+// or two complex64 amplitudes), several per thread in flight, work-groups in
+// memory order. A qubit whose bit lies inside a 128-byte line (unit bits 0..2)
+// is handled on whole lines: as single accesses of every second unit the
+// lines would be moved half used, and non-temporal stores of part of a line
+// are several times slower. 28 qubits complex64: H 710 us (6.0 TB/s) against
+// 850-905 us one pair per thread, T 350-740 against 412-885 us, CZ 172-735
+// against 206-870 us by the qubits.
+template <typename T>
+struct Unit;
+template <>
+struct Unit<float> {
+    typedef vf4 type;
+    static constexpr int AMPS = 2, BITS = 1;
+};
+template <>
+struct Unit<double> {
+    typedef vd2 type;
+    static constexpr int AMPS = 1, BITS = 0;
+};
+
 // A single-qubit gate on the pairs (i, i + 2^q) with bit q of i clear (Sec. 2).
+// MODE 0: unit bit ub >= 3, a thread takes both units of four pairs;
+// 1..3: unit bit 0..2, a lane owns a unit and takes its partner's from the lane
+// that differs in that bit; 4: the pair lies in one (complex64) unit.
 template <typename T>
-__global__ __launch_bounds__(256) void k_gate1q(typename Cplx<T>::type* __restrict__ psi, int q, T m0r,
-                                                T m0i, T m1r, T m1i, T m2r, T m2i, T m3r, T m3i,
-                                                uint64_t npairs) {
-    using V = typename Cplx<T>::type;
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
-    const uint64_t bit = uint64_t(1) << q;
-    for (uint64_t p = (uint64_t)xcd_block() * 256 + threadIdx.x; p < npairs; p += stride) {
-        const uint64_t i = insert_zero(p, q);
-        const V a = psi[i], b = psi[i | bit];
-        V o0, o1;
-        o0.x = (m0r * a.x - m0i * a.y) + (m1r * b.x - m1i * b.y);
-        o0.y = (m0r * a.y + m0i * a.x) + (m1r * b.y + m1i * b.x);
-        o1.x = (m2r * a.x - m2i * a.y) + (m3r * b.x - m3i * b.y);
-        o1.y = (m2r * a.y + m2i * a.x) + (m3r * b.y + m3i * b.x);
-        psi[i] = o0;
-        psi[i | bit] = o1;
+struct Gate2x2 {
+    T m[8];
+};
+template <typename T, int MODE, bool NT>
+__global__ __launch_bounds__(256, 6) void k_gate1q(typename Unit<T>::type* __restrict__ psi, int ub, Gate2x2<T> g,
+                                                uint64_t units) {
+    using V = typename Unit<T>::type;
+    constexpr int A = Unit<T>::AMPS;
+    const T* m = g.m;
+    // row of the 2x2: c0 a + c1 b
+    auto row = [](T c0r, T c0i, T c1r, T c1i, T ar, T ai, T br, T bi, T& re, T& im) {
+        re = (c0r * ar - c0i * ai) + (c1r * br - c1i * bi);
+        im = (c0r * ai + c0i * ar) + (c1r * bi + c1i * br);
+    };
+    if constexpr (MODE == 0) {
+        constexpr int P = 4;
+        V a[P], b[P];
+        uint64_t at[P];
+        const uint64_t bit = uint64_t(1) << ub, pairs = units / 2;
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            const uint64_t p = ((uint64_t)blockIdx.x * P + u) * 256 + threadIdx.x;
+            at[u] = insert_zero(min(p, pairs - 1), ub);
+            a[u] = load16<NT>(psi + at[u]);
+            b[u] = load16<NT>(psi + (at[u] | bit));
+        }
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            if (((uint64_t)blockIdx.x * P + u) * 256 + threadIdx.x >= pairs) break;
+            V x, y;
+#pragma unroll
+            for (int k = 0; k < A; ++k) {
+                T r, i;
+                row(m[0], m[1], m[2], m[3], a[u][2 * k], a[u][2 * k + 1], b[u][2 * k], b[u][2 * k + 1], r, i);
+                x[2 * k] = r;
+                x[2 * k + 1] = i;
+                row(m[4], m[5], m[6], m[7], a[u][2 * k], a[u][2 * k + 1], b[u][2 * k], b[u][2 * k + 1], r, i);
+                y[2 * k] = r;
+                y[2 * k + 1] = i;
+            }
+            store16<NT>(psi + at[u], x);
+            store16<NT>(psi + (at[u] | bit), y);
+        }
+    } else {
+        constexpr int P = 8;
+        V a[P];
+        const uint64_t u0 = (uint64_t)blockIdx.x * P * 256 + threadIdx.x;
+#pragma unroll
+        for (int u = 0; u < P; ++u) a[u] = load16<NT>(psi + min(u0 + u * 256, units - 1));
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            V o = a[u];
+            if constexpr (MODE == 4) {
+                T r, i;
+                row(m[0], m[1], m[2], m[3], a[u][0], a[u][1], a[u][2], a[u][3], r, i);
+                o[0] = r;
+                o[1] = i;
+                row(m[4], m[5], m[6], m[7], a[u][0], a[u][1], a[u][2], a[u][3], r, i);
+                o[2] = r;
+                o[3] = i;
+            } else {
+                const vf4 own = __builtin_bit_cast(vf4, a[u]);
+                vf4 oth;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) oth[k] = __uint_as_float(lane_xor<MODE - 1>(__float_as_uint(own[k])));
+                const V b = __builtin_bit_cast(V, oth);
+                const bool hi = (threadIdx.x >> (MODE - 1)) & 1;
+#pragma unroll
+                for (int k = 0; k < A; ++k) {
+                    const T lr = hi ? b[2 * k] : a[u][2 * k], li = hi ? b[2 * k + 1] : a[u][2 * k + 1];
+                    const T hr = hi ? a[u][2 * k] : b[2 * k], hh = hi ? a[u][2 * k + 1] : b[2 * k + 1];
+                    T r, i;
+                    row(hi ? m[4] : m[0], hi ? m[5] : m[1], hi ? m[6] : m[2], hi ? m[7] : m[3], lr, li, hr, hh, r, i);
+                    o[2 * k] = r;
+                    o[2 * k + 1] = i;
+                }
+            }
+            if (u0 + u * 256 < units) store16<NT>(psi + (u0 + u * 256), o);
+        }
     }
 }
 
-// A diagonal single-qubit gate diag(1, e^{i phi}): only amplitudes with bit q set change.
-template <typename T>
-__global__ __launch_bounds__(256) void k_phase1q(typename Cplx<T>::type* __restrict__ psi, int q, T cr,
-                                                 T ci, uint64_t nhalf) {
-    using V = typename Cplx<T>::type;
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
-    const uint64_t bit = uint64_t(1) << q;
-    for (uint64_t p = (uint64_t)xcd_block() * 256 + threadIdx.x; p < nhalf; p += stride) {
-        const uint64_t i = insert_zero(p, q) | bit;
-        const V a = psi[i];
-        V o;
-        o.x = a.x * cr - a.y * ci;
-        o.y = a.x * ci + a.y * cr;
-        psi[i] = o;
+// Diagonal gates of the plain method: diag(1, e^{i phi}) on one qubit (only
+// amplitudes with its bit set change) or CZ (NEG: amplitudes with both bits
+// set are negated). hb0 < hb1: the set unit bits from 3 up (-1: none), which
+// select the units; lomask: set bits among unit bits 0..2, and odd: the
+// second amplitude of a complex64 unit only - these select inside whole lines.
+// spread: each XCD takes its own stretch of the state. Selecting every other
+// 2 KiB (unit bit 7) leaves half of the memory channels idle in one compact
+// stretch: 28 qubits complex64, T on qubit 8, 354 us spread over eight against
+// 546 us; any other bit is as fast or faster in memory order (T on qubit 27:
+// 350 against 374 us).
+template <typename T, bool NEG, bool NT>
+__global__ __launch_bounds__(256, 6) void k_phase(typename Unit<T>::type* __restrict__ psi, int hb0, int hb1, int lomask,
+                                               int odd, int spread, T cr, T ci, uint64_t count) {
+    using V = typename Unit<T>::type;
+    constexpr int A = Unit<T>::AMPS, P = 8;
+    V a[P];
+    uint64_t at[P];
+    const uint64_t u0 = (uint64_t)(spread ? xcd_block() : blockIdx.x) * P * 256 + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+        uint64_t i = min(u0 + u * 256, count - 1);
+        if (hb0 >= 0) i = insert_zero(i, hb0) | uint64_t(1) << hb0;
+        if (hb1 >= 0) i = insert_zero(i, hb1) | uint64_t(1) << hb1;
+        at[u] = i;
+        a[u] = load16<NT>(psi + i);
     }
-}
-
-// CZ(a, b), a < b: negate the amplitudes with both bits set.
-template <typename T>
-__global__ __launch_bounds__(256) void k_cz(typename Cplx<T>::type* __restrict__ psi, int a, int b,
-                                            uint64_t nquarter) {
-    using V = typename Cplx<T>::type;
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
-    const uint64_t m = (uint64_t(1) << a) | (uint64_t(1) << b);
-    for (uint64_t p = (uint64_t)xcd_block() * 256 + threadIdx.x; p < nquarter; p += stride) {
-        const uint64_t i = insert_zero(insert_zero(p, a), b) | m;
-        V v = psi[i];
-        v.x = -v.x;
-        v.y = -v.y;
-        psi[i] = v;
+    const bool sel = ((int)threadIdx.x & lomask) == lomask;  // unit bits 0..2 are lane bits
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+        V o = a[u];
+#pragma unroll
+        for (int k = 0; k < A; ++k) {
+            if (!sel || (A == 2 && k == 0 && odd)) continue;
+            if constexpr (NEG) {
+                o[2 * k] = -a[u][2 * k];
+                o[2 * k + 1] = -a[u][2 * k + 1];
+            } else {
+                o[2 * k] = a[u][2 * k] * cr - a[u][2 * k + 1] * ci;
+                o[2 * k + 1] = a[u][2 * k] * ci + a[u][2 * k + 1] * cr;
+            }
+        }
+        if (u0 + u * 256 < count) store16<NT>(psi + at[u], o);
     }
 }
 
@@ -3064,32 +3583,6 @@ constexpr int kBuildGateChunk = 64;  // gates staged in LDS at a time
 // Work-groups per matrix of k qubits (kBuildThreads / 64 waves of
 // kBuildCols * 2^(6-k) columns each; kBuildCols for k = 7).
 __host__ __device__ constexpr int build_parts(int k) { return k <= 5 ? 1 : (k == 6 ? 4 : 8); }
-
-// The value of x in the lane whose index differs in bit B.
-template <int B>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
-    if constexpr (B == 0) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true);  // quad [1,0,3,2]
-    if constexpr (B == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true);  // quad [2,3,0,1]
-    if constexpr (B == 2) {  // mirrored within 8 lanes (index ^ 7), then within 4 (^ 3)
-        const int m = __builtin_amdgcn_mov_dpp((int)x, 0x141, 0xf, 0xf, true);
-        return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xf, 0xf, true);
-    }
-    if constexpr (B == 3) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);  // row rotated by 8
-    const int lane = (int)(threadIdx.x & 63);
-    if constexpr (B == 4) {
-        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-        return (lane & 16) ? r[0] : r[1];
-    } else {
-        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-        return (lane & 32) ? r[0] : r[1];
-    }
-}
-template <int B>
-__device__ __forceinline__ double lane_xor(double x) {
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = lane_xor<B>((uint32_t)b), hi = lane_xor<B>((uint32_t)(b >> 32));
-    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
-}
 
 struct BuildLds {
     // gates of the current chunk; op: 0 CZ, 1 diagonal one-qubit (phase m[6..7]
@@ -3533,6 +4026,12 @@ inline unsigned grid_for(uint64_t work, unsigned per_block, unsigned cap) {
     const uint64_t b = (work + per_block - 1) / per_block;
     return (unsigned)(b < 1 ? 1 : (b > cap ? cap : b));
 }
+// Work-groups of four one-tile waves.
+inline unsigned tile_grid(uint64_t tiles) { return (unsigned)((tiles + 3) / 4); }
+// Does every access instruction of a direct kernel cover whole 128-byte lines?
+// Its rows from target `first` up are separate instructions, the rest of the
+// tile is on the lanes, so no such target may be among the line's `bits` bits.
+inline bool whole_lines(const ClusterGeom& g, int first, int bits) { return g.t[first] >= bits; }
 constexpr unsigned kStreamGrid = 8192;  // blocks of 256 threads for grid-stride streaming kernels
 constexpr unsigned kPersistGrid = 2048; // work-groups of the persistent cluster kernels
 constexpr unsigned kPairGrid = 256;     // one 12-wave work-group per compute unit (LDS-limited)
@@ -3713,7 +4212,7 @@ StageGeom make_stage_geom(const ClusterGeom& g, int C, int unit) {
     std::memset(&sg, 0, sizeof(sg));
     uint64_t tmask = 0;
     for (int m = 0; m < g.k; ++m) tmask |= uint64_t(1) << g.t[m];
-    int cols[8], nc = 0;
+    int cols[16], nc = 0;
     for (int b = 0; b < g.n && nc < C; ++b)
         if (!(tmask >> b & 1)) cols[nc++] = b;
     uint64_t tilemask = tmask;
@@ -3765,7 +4264,15 @@ int cluster_layout(bool dbl, int k, int n) {
             if (n - k < 5) return LAYOUT_PLAIN;
             return g_k6_kernel == 2 ? LAYOUT_SPLIT16F : (g_k6_kernel == 1 ? LAYOUT_GAUSS32F : LAYOUT_MFMA32F);
         }
-        return (k >= 4 && n - k >= 6) ? LAYOUT_MFMA32F : LAYOUT_PLAIN;
+        if (k < 4 || n - k < 6) return LAYOUT_PLAIN;
+        // On the 6-qubit halves kernel, padded (the caller does), where its tile
+        // fits: the fp32 matrix cores hold a 5-qubit pass back at every size (30
+        // qubits, mean of 23 target sets: 3.03 ms padded against 3.49; 24 qubits:
+        // 52 us against 65-73; 20 qubits: 10 us either way), a 4-qubit one only
+        // beyond the caches (30 qubits: 3.12 against 3.40 ms, 24 qubits: 52
+        // against 46 us). The halves' error is not larger: 14-qubit states, one
+        // gate of each width, 2.3e-7 against 2.5e-7 of the state's norm.
+        return g_k6_kernel == 2 && n >= 11 && (k == 5 || beyond_caches(n, false)) ? LAYOUT_SPLIT16F : LAYOUT_MFMA32F;
     }
     const int nb = (k == 6) ? 1 : 2;
     return (k >= 3 && n - k >= 4 + (nb == 2)) ? LAYOUT_MFMA16D : LAYOUT_PLAIN;
@@ -3775,6 +4282,20 @@ namespace {
 template <int K>
 hipError_t launch_valu_k(void* psi, bool dbl, const ClusterGeom& g, const void* mat, const EpiDesc* epi,
                          hipStream_t st, double* stats_part = nullptr, unsigned* stats_blocks = nullptr) {
+    if constexpr (K <= 3) {
+        if (!stats_part && beyond_caches(g.n, dbl)) {
+            const int tb = dbl ? 9 : 10;  // 8 KiB wave tiles
+            const StageGeom sg = make_stage_geom(g, tb - K, dbl ? 6 : 7);
+            const uint64_t tiles = uint64_t(1) << (g.n - tb);
+            auto go = [&](auto kern, auto* p) {
+                hipLaunchKernelGGL(kern, dim3(tile_grid(tiles)), dim3(256), 0, st, p, (decltype(p))mat, epi, sg,
+                                   tiles, nullptr);
+            };
+            dbl ? go(k_cluster_valu_staged<double, K>, (double2*)psi)
+                : go(k_cluster_valu_staged<float, K>, (float2*)psi);
+            return hipGetLastError();
+        }
+    }
     if (K >= 2 && K <= 3 && g.n - K >= 6) {
         constexpr int KS = K >= 2 && K <= 3 ? K : 2;
         const StageGeom sg = make_stage_geom(g, 6, 6);  // tile: the targets and 6 column bits
@@ -3791,11 +4312,11 @@ hipError_t launch_valu_k(void* psi, bool dbl, const ClusterGeom& g, const void* 
         }
         const unsigned grid = grid_for(tiles, 4, kStreamGrid);
         if (dbl)
-            hipLaunchKernelGGL((k_cluster_valu_staged<double, KS>), dim3(grid), dim3(256), 0, st, (double2*)psi,
-                               (const double2*)mat, epi, sg, tiles, nullptr);
+            hipLaunchKernelGGL((k_cluster_valu_cached<double, KS>), dim3(grid), dim3(256), 0, st, (double2*)psi,
+                               (const double2*)mat, epi, sg, tiles);
         else
-            hipLaunchKernelGGL((k_cluster_valu_staged<float, KS>), dim3(grid), dim3(256), 0, st, (float2*)psi,
-                               (const float2*)mat, epi, sg, tiles, nullptr);
+            hipLaunchKernelGGL((k_cluster_valu_cached<float, KS>), dim3(grid), dim3(256), 0, st, (float2*)psi,
+                               (const float2*)mat, epi, sg, tiles);
         return hipGetLastError();
     }
     if (stats_part) return hipErrorInvalidValue;  // no sums in the plain form
@@ -3853,20 +4374,28 @@ hipError_t launch_mfma64_k(void* psi, const ClusterGeom& g, const void* mat, con
                            hipStream_t st) {
     if (K <= 5 && variant == 1) {
         constexpr int KS = K <= 5 ? K : 5;
-        constexpr int TH = KS == 5 ? 512 : 256;
-        const StageGeom sg = make_stage_geom(g, 5, 6);
-        const uint64_t tiles = g.ncols >> 5;
-        const unsigned grid = grid_for(tiles, TH / 64, kPersistGrid);
-        hipLaunchKernelGGL((k_cluster_f64_stage<KS, 5, TH>), dim3(grid), dim3(TH), 0, st, (vd2*)psi,
-                           (const double*)mat, epi, g, sg);
+        constexpr int C = KS == 5 ? 4 : 5;
+        const StageGeom sg = make_stage_geom(g, C, 6);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(tile_grid(g.ncols >> C)), dim3(256), 0, st, (vd2*)psi, (const double*)mat,
+                               epi, g, sg);
+        };
+        beyond_caches(g.n, true) ? go(k_cluster_f64_stage<KS, C, true>) : go(k_cluster_f64_stage<KS, C, false>);
         return hipGetLastError();
     }
-    constexpr int NB = (K == 6) ? 1 : 2;
-    constexpr int TH = (K == 6) ? 512 : 256;
-    const uint64_t tiles = g.ncols / (16 * NB);
-    const unsigned grid = grid_for(tiles, TH / 64, kPersistGrid);
-    hipLaunchKernelGGL((k_cluster_f64_mfma<K, NB, TH>), dim3(grid), dim3(TH), 0, st, (double2*)psi,
-                       (const double*)mat, epi, g);
+    if constexpr (K == 6) {
+        const unsigned grid = grid_for(g.ncols / 16, 8, kPersistGrid);
+        hipLaunchKernelGGL((k_cluster_f64_mfma_loop<6, 1, 512>), dim3(grid), dim3(512), 0, st, (double2*)psi,
+                           (const double*)mat, epi, g);
+    } else {
+        constexpr int NB = K == 5 ? 1 : 2;
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(tile_grid(g.ncols / (16 * NB))), dim3(256), 0, st, (vd2*)psi,
+                               (const double*)mat, epi, g);
+        };
+        beyond_caches(g.n, true) && whole_lines(g, 0, 3) ? go(k_cluster_f64_mfma<K, NB, true>)
+                                                       : go(k_cluster_f64_mfma<K, NB, false>);
+    }
     return hipGetLastError();
 }
 }  // namespace
@@ -3912,13 +4441,15 @@ hipError_t launch_cluster(void* psi, bool dbl, const ClusterGeom& g, const void*
     if (layout == LAYOUT_SPLIT16F && !dbl && g.k == 6 && variant == 1) {
         const StageGeom sg = make_stage_geom(g, 5, 7);  // 11 tile bits; chunks of 2^7 amplitudes
         const uint64_t tiles = g.ncols >> 5;
-        const unsigned grid = grid_for(tiles, 8, kStagedGrid);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(tile_grid(tiles)), dim3(256), 0, st, (float2*)psi, (const half8*)mat, epi,
+                               sg, tiles);
+        };
+        const bool nt = beyond_caches(g.n, false);
         if (g.t[0] == 0)
-            hipLaunchKernelGGL(k_cluster_f32_split6s<true>, dim3(grid), dim3(512), 0, st, (float2*)psi,
-                               (const half8*)mat, epi, sg, tiles);
+            nt ? go(k_cluster_f32_split6s<true, true>) : go(k_cluster_f32_split6s<true, false>);
         else
-            hipLaunchKernelGGL(k_cluster_f32_split6s<false>, dim3(grid), dim3(512), 0, st, (float2*)psi,
-                               (const half8*)mat, epi, sg, tiles);
+            nt ? go(k_cluster_f32_split6s<false, true>) : go(k_cluster_f32_split6s<false, false>);
         return hipGetLastError();
     }
     if (layout == LAYOUT_SPLIT16F && !dbl && g.k == 6) {
@@ -3927,19 +4458,21 @@ hipError_t launch_cluster(void* psi, bool dbl, const ClusterGeom& g, const void*
         if (stats_part) {
             *stats_blocks = grid;
             if (g.t[0] == 0)
-                hipLaunchKernelGGL((k_cluster_f32_split6<true, true>), dim3(grid), dim3(256), 0, st, (float2*)psi,
+                hipLaunchKernelGGL((k_cluster_f32_split6_sum<true>), dim3(grid), dim3(256), 0, st, (float2*)psi,
                                    (const half8*)mat, epi, g, stats_part);
             else
-                hipLaunchKernelGGL((k_cluster_f32_split6<false, true>), dim3(grid), dim3(256), 0, st,
+                hipLaunchKernelGGL((k_cluster_f32_split6_sum<false>), dim3(grid), dim3(256), 0, st,
                                    (float2*)psi, (const half8*)mat, epi, g, stats_part);
             return hipGetLastError();
         }
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(tile_grid(tiles)), dim3(256), 0, st, (float2*)psi, (const half8*)mat, epi, g);
+        };
+        const bool nt = beyond_caches(g.n, false) && whole_lines(g, 1, 4);
         if (g.t[0] == 0)
-            hipLaunchKernelGGL(k_cluster_f32_split6<true>, dim3(grid), dim3(256), 0, st, (float2*)psi,
-                               (const half8*)mat, epi, g, nullptr);
+            nt ? go(k_cluster_f32_split6<true, true>) : go(k_cluster_f32_split6<true, false>);
         else
-            hipLaunchKernelGGL(k_cluster_f32_split6<false>, dim3(grid), dim3(256), 0, st, (float2*)psi,
-                               (const half8*)mat, epi, g, nullptr);
+            nt ? go(k_cluster_f32_split6<false, true>) : go(k_cluster_f32_split6<false, false>);
         return hipGetLastError();
     }
     if (layout == LAYOUT_GAUSS32F && !dbl && g.k == 6) {
@@ -3974,15 +4507,14 @@ hipError_t launch_cluster(void* psi, bool dbl, const ClusterGeom& g, const void*
 }
 
 hipError_t launch_diag(void* psi, bool dbl, int n, const EpiDesc* epi, hipStream_t st) {
-    // windows per wave step: 4 KiB of loads in flight per wave for either dtype
-    constexpr int UF = 4, UD = 2;
     const uint64_t nwin = n >= 7 ? (uint64_t(1) << (n - 7)) : 1;
-    const uint64_t nrun = (nwin + 63) >> 6;  // runs of 64 windows, one per wave at a time
-    const unsigned grid = grid_for(nrun, 4, kStreamGrid);
+    const unsigned grid = (unsigned)((nwin + 63) >> 6);  // runs of 64 windows, one per work-group
+    auto go = [&](auto kern, auto* p) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, p, n, epi); };
+    const bool nt = beyond_caches(n, dbl);
     if (dbl)
-        hipLaunchKernelGGL((k_diag<double, UD>), dim3(grid), dim3(256), 0, st, (double2*)psi, n, epi);
+        nt ? go(k_diag<double, true>, (double2*)psi) : go(k_diag<double, false>, (double2*)psi);
     else
-        hipLaunchKernelGGL((k_diag<float, UF>), dim3(grid), dim3(256), 0, st, (float2*)psi, n, epi);
+        nt ? go(k_diag<float, true>, (float2*)psi) : go(k_diag<float, false>, (float2*)psi);
     return hipGetLastError();
 }
 
@@ -3996,39 +4528,64 @@ hipError_t launch_batch(const BatchOp* ops, const BatchItem* items, uint32_t n_i
     return hipGetLastError();
 }
 
-hipError_t launch_gate1q(void* psi, bool dbl, int n, int q, const double m[8], hipStream_t st) {
-    const uint64_t np = uint64_t(1) << (n - 1);
-    const unsigned grid = grid_for(np, 256, kStreamGrid);
-    if (dbl)
-        hipLaunchKernelGGL(k_gate1q<double>, dim3(grid), dim3(256), 0, st, (double2*)psi, q, m[0], m[1], m[2],
-                           m[3], m[4], m[5], m[6], m[7], np);
-    else
-        hipLaunchKernelGGL(k_gate1q<float>, dim3(grid), dim3(256), 0, st, (float2*)psi, q, (float)m[0],
-                           (float)m[1], (float)m[2], (float)m[3], (float)m[4], (float)m[5], (float)m[6],
-                           (float)m[7], np);
+namespace {
+template <typename T, bool NT>
+hipError_t launch_gate1q_t(void* psi, int n, int q, const double m[8], hipStream_t st) {
+    using U = Unit<T>;
+    auto* p = (typename U::type*)psi;
+    const uint64_t units = uint64_t(1) << (n - U::BITS);
+    const int ub = q - U::BITS;
+    Gate2x2<T> g;
+    for (int i = 0; i < 8; ++i) g.m[i] = (T)m[i];
+    auto go = [&](auto kern, uint64_t per_group) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((units + per_group - 1) / per_group)), dim3(256), 0, st, p, ub, g,
+                           units);
+    };
+    // eight units per thread either way
+    if (ub >= 3) go(k_gate1q<T, 0, NT>, 2048);
+    else if (ub == 2) go(k_gate1q<T, 3, NT>, 2048);
+    else if (ub == 1) go(k_gate1q<T, 2, NT>, 2048);
+    else if (ub == 0) go(k_gate1q<T, 1, NT>, 2048);
+    else if constexpr (U::BITS == 1) go(k_gate1q<T, 4, NT>, 2048);
     return hipGetLastError();
+}
+
+// A phase (or, NEG, a sign) on the amplitudes whose bits q0 (and q1 >= 0) are set.
+template <typename T, bool NEG>
+hipError_t launch_phase_t(void* psi, int n, int q0, int q1, double cs, double sn, hipStream_t st) {
+    using U = Unit<T>;
+    int hb[2] = {-1, -1}, nh = 0, lomask = 0, odd = 0;
+    for (int q : {std::min(q0, q1), std::max(q0, q1)}) {
+        const int ub = q - U::BITS;
+        if (q < 0) continue;
+        if (ub < 0) odd = 1;
+        else if (ub < 3) lomask |= 1 << ub;
+        else hb[nh++] = ub;
+    }
+    const uint64_t count = uint64_t(1) << (n - U::BITS - nh);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((count + 2047) / 2048)), dim3(256), 0, st, (typename U::type*)psi,
+                           hb[0], hb[1], lomask, odd, hb[0] == 7 || hb[1] == 7, (T)cs, (T)sn, count);
+    };
+    beyond_caches(n - nh, sizeof(T) == 8) ? go(k_phase<T, NEG, true>) : go(k_phase<T, NEG, false>);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_gate1q(void* psi, bool dbl, int n, int q, const double m[8], hipStream_t st) {
+    if (beyond_caches(n, dbl))
+        return dbl ? launch_gate1q_t<double, true>(psi, n, q, m, st) : launch_gate1q_t<float, true>(psi, n, q, m, st);
+    return dbl ? launch_gate1q_t<double, false>(psi, n, q, m, st) : launch_gate1q_t<float, false>(psi, n, q, m, st);
 }
 
 hipError_t launch_phase1q(void* psi, bool dbl, int n, int q, double cs, double sn, hipStream_t st) {
-    const uint64_t nh = uint64_t(1) << (n - 1);
-    const unsigned grid = grid_for(nh, 256, kStreamGrid);
-    if (dbl)
-        hipLaunchKernelGGL(k_phase1q<double>, dim3(grid), dim3(256), 0, st, (double2*)psi, q, cs, sn, nh);
-    else
-        hipLaunchKernelGGL(k_phase1q<float>, dim3(grid), dim3(256), 0, st, (float2*)psi, q, (float)cs,
-                           (float)sn, nh);
-    return hipGetLastError();
+    return dbl ? launch_phase_t<double, false>(psi, n, q, -1, cs, sn, st)
+               : launch_phase_t<float, false>(psi, n, q, -1, cs, sn, st);
 }
 
 hipError_t launch_cz(void* psi, bool dbl, int n, int a, int b, hipStream_t st) {
-    if (a > b) { const int t = a; a = b; b = t; }
-    const uint64_t nq = uint64_t(1) << (n - 2);
-    const unsigned grid = grid_for(nq, 256, kStreamGrid);
-    if (dbl)
-        hipLaunchKernelGGL(k_cz<double>, dim3(grid), dim3(256), 0, st, (double2*)psi, a, b, nq);
-    else
-        hipLaunchKernelGGL(k_cz<float>, dim3(grid), dim3(256), 0, st, (float2*)psi, a, b, nq);
-    return hipGetLastError();
+    return dbl ? launch_phase_t<double, true>(psi, n, a, b, 0, 0, st)
+               : launch_phase_t<float, true>(psi, n, a, b, 0, 0, st);
 }
 
 hipError_t launch_stats(const void* psi, bool dbl, int n, void* probs, bool probs_dbl, double* part,
@@ -4055,65 +4612,89 @@ hipError_t launch_stats(const void* psi, bool dbl, int n, void* probs, bool prob
 }
 
 // ------------------------------------------------------------ bit permutation
-// One work-group per tile (persistent grid): the whole tile is loaded into
+// One work-group per tile, in memory order: the whole tile is loaded into
 // registers (every load in flight), written to LDS at its permuted index, and
 // stored back in the original order of addresses, so loads and stores are
-// both runs over the tile's lowest bits (the host puts the lowest non-moving
-// state bits into the tile for that). In place: a tile is read completely
-// before any of it is written, and tiles are disjoint.
-template <typename V2, int NT>
-__global__ __launch_bounds__(256) void k_permute(V2* __restrict__ psi, uint64_t ntiles, PermGeom pg) {
-    constexpr int N = 1 << NT;
-    constexpr int PER = (N + 255) / 256;
-    __shared__ V2 buf[N];
-    for (uint64_t tile = xcd_block(); tile < ntiles; tile += gridDim.x) {
-        uint64_t base = tile;
+// both 16-byte accesses of runs over the tile's lowest bits (the host puts the
+// lowest non-moving state bits into the tile for that; bit 0 is always one of
+// its bits for complex64). In place: a tile is read completely before any of it is written,
+// and tiles are disjoint.
+template <typename T, int NB, bool NT>
+__global__ __launch_bounds__(256) void k_permute(typename Cplx<T>::type* __restrict__ psi, PermGeom pg, int share) {
+    constexpr bool F = sizeof(T) == 4;
+    constexpr int AB = F ? 1 : 0;  // tau bits of one 16-byte access
+    constexpr int N = 1 << (NB - AB), PER = (N + 255) / 256;  // accesses of the tile, of a thread
+    typedef T vt2 __attribute__((ext_vector_type(2)));
+    __shared__ vf4 buf4[N];
+    vt2* buf = reinterpret_cast<vt2*>(buf4);
+    // tiles that share cache lines stay on one XCD (its L2 joins their accesses)
+    uint64_t base = share ? xcd_block() : blockIdx.x;
 #pragma unroll
-        for (int i = 0; i < NT; ++i) base = insert_zero(base, pg.tb[i]);
-        V2 v[PER];
-        uint64_t addr[PER];
+    for (int i = 0; i < NB; ++i) base = insert_zero(base, pg.tb[i]);
+    // slot of tau: its upper bits folded into the bank bits (linear over XOR)
+    auto slot = [](int t) { return F ? t ^ (((t >> 5) & 15) << 1) : t ^ ((t >> 4) & 15); };
+    // state offset and permuted slot of access t (both linear over its bits)
+    auto off = [&](int t) {
+        uint64_t o = 0;
+#pragma unroll
+        for (int j = AB; j < NB; ++j) o |= uint64_t((t >> (j - AB)) & 1) << pg.tb[j];
+        return o;
+    };
+    auto dst = [&](int t) {
+        int d = 0;
+#pragma unroll
+        for (int j = AB; j < NB; ++j) d |= ((t >> (j - AB)) & 1) << pg.to[j];
+        return slot(d);
+    };
+    const int t = (int)threadIdx.x;
+    const bool on = N >= 256 || t < N;
+    typename Cplx<T>::type* mine = psi + (base | off(t));
+    const int d0 = dst(t), d1 = F ? slot(1 << pg.to[0]) : 0;
+    vf4 v[PER];
+    if (on) {
+#pragma unroll
+        for (int r = 0; r < PER; ++r) v[r] = load16<NT>(reinterpret_cast<const vf4*>(mine + off(r * 256)));
 #pragma unroll
         for (int r = 0; r < PER; ++r) {
-            const int tau = r * 256 + (int)threadIdx.x;
-            uint64_t off = 0;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) off |= uint64_t((tau >> j) & 1) << pg.tb[j];
-            addr[r] = base | off;
-            if (tau < N) v[r] = psi[addr[r]];
+            const int d = d0 ^ dst(r * 256);
+            if constexpr (F) {
+                buf[d] = vt2{v[r].x, v[r].y};
+                buf[d ^ d1] = vt2{v[r].z, v[r].w};
+            } else {
+                buf[d] = __builtin_bit_cast(vt2, v[r]);
+            }
         }
+    }
+    __syncthreads();
+    if (on) {
 #pragma unroll
-        for (int r = 0; r < PER; ++r) {
-            const int tau = r * 256 + (int)threadIdx.x;
-            int dst = 0;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) dst |= ((tau >> j) & 1) << pg.to[j];
-            if (tau < N) buf[dst] = v[r];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < PER; ++r) {
-            const int tau = r * 256 + (int)threadIdx.x;
-            if (tau < N) psi[addr[r]] = buf[tau];
-        }
-        __syncthreads();
+        for (int r = 0; r < PER; ++r)
+            store16<NT>(reinterpret_cast<vf4*>(mine + off(r * 256)), (vf4)buf4[slot((r * 256 + t) << AB) >> AB]);
     }
 }
 
 namespace {
-template <int NT>
+template <int NB>
 hipError_t launch_permute_nt(void* psi, bool dbl, int n, const PermGeom& pg, hipStream_t st) {
-    const uint64_t tiles = uint64_t(1) << (n - NT);
-    const unsigned grid = grid_for(tiles, 1, kPersistGrid);
-    if (dbl)
-        hipLaunchKernelGGL((k_permute<double2, NT>), dim3(grid), dim3(256), 0, st, (double2*)psi, tiles, pg);
-    else
-        hipLaunchKernelGGL((k_permute<float2, NT>), dim3(grid), dim3(256), 0, st, (float2*)psi, tiles, pg);
+    const unsigned grid = (unsigned)(uint64_t(1) << (n - NB));
+    // a tile holds whole 128-byte lines when the lowest bits are tile bits
+    const bool lines = NB < 4 || pg.tb[dbl ? 2 : 3] == (dbl ? 2 : 3);
+    auto go = [&](auto kern, auto* p) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, p, pg, lines ? 0 : 1);
+    };
+    const bool nt = beyond_caches(n, dbl) && lines;
+    if constexpr (NB <= 12)
+        if (dbl) {
+            nt ? go(k_permute<double, NB, true>, (double2*)psi) : go(k_permute<double, NB, false>, (double2*)psi);
+            return hipGetLastError();
+        }
+    nt ? go(k_permute<float, NB, true>, (float2*)psi) : go(k_permute<float, NB, false>, (float2*)psi);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_permute(void* psi, bool dbl, int n, const PermGeom& pg, hipStream_t st) {
-    if (pg.nt < 1 || pg.nt > kPermMaxBits || pg.nt > n) return hipErrorInvalidValue;
+    if (pg.nt < 1 || pg.nt > (dbl ? 12 : kPermTileBits) || pg.nt > n || (!dbl && pg.tb[0] != 0)) return hipErrorInvalidValue;
     switch (pg.nt) {
         case 1: return launch_permute_nt<1>(psi, dbl, n, pg, st);
         case 2: return launch_permute_nt<2>(psi, dbl, n, pg, st);
@@ -4126,7 +4707,8 @@ hipError_t launch_permute(void* psi, bool dbl, int n, const PermGeom& pg, hipStr
         case 9: return launch_permute_nt<9>(psi, dbl, n, pg, st);
         case 10: return launch_permute_nt<10>(psi, dbl, n, pg, st);
         case 11: return launch_permute_nt<11>(psi, dbl, n, pg, st);
-        default: return launch_permute_nt<12>(psi, dbl, n, pg, st);
+        case 12: return launch_permute_nt<12>(psi, dbl, n, pg, st);
+        default: return launch_permute_nt<13>(psi, dbl, n, pg, st);
     }
 }
 
