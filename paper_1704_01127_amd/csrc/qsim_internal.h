@@ -114,11 +114,24 @@ struct BuildOp {
 
 // Geometry of one cluster application.
 struct ClusterGeom {
-    int32_t t[kMaxK];   // sorted target qubits
+    int32_t t[kMaxK];   // target qubits: bit j of the matrix index is qubit t[j]
+    int32_t srt[kMaxK]; // the same, ascending (where the column bits leave gaps)
     int32_t n;          // qubits of the state
     int32_t k;
     uint64_t ncols;     // 2^(n-k)
 };
+inline void set_geom(ClusterGeom& g, int n, int k, const int* t) {
+    for (int j = 0; j < kMaxK; ++j) g.t[j] = g.srt[j] = j < k ? t[j] : 0;
+    for (int i = 1; i < k; ++i)
+        for (int j = i; j > 0 && g.srt[j] < g.srt[j - 1]; --j) {
+            const int32_t x = g.srt[j];
+            g.srt[j] = g.srt[j - 1];
+            g.srt[j - 1] = x;
+        }
+    g.n = n;
+    g.k = k;
+    g.ncols = uint64_t(1) << (n - k);
+}
 
 // Geometry of the LDS-staged cluster kernels. A wave tile is the set of
 // amplitudes whose "tile bits" (the k targets and the C lowest non-target

@@ -59,7 +59,7 @@ __device__ __forceinline__ uint64_t insert_zero(uint64_t c, int t) {
 template <int K>
 __device__ __forceinline__ uint64_t deposit_cols(uint64_t c, const ClusterGeom& g) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) c = insert_zero(c, g.t[j]);
+    for (int j = 0; j < K; ++j) c = insert_zero(c, g.srt[j]);
     return c;
 }
 
@@ -4270,8 +4270,8 @@ int cluster_layout(bool dbl, int k, int n) {
         // qubits, mean of 23 target sets: 3.03 ms padded against 3.49; 24 qubits:
         // 52 us against 65-73; 20 qubits: 10 us either way), a 4-qubit one only
         // beyond the caches (30 qubits: 3.12 against 3.40 ms, 24 qubits: 52
-        // against 46 us). The halves' error is not larger: 14-qubit states, one
-        // gate of each width, 2.3e-7 against 2.5e-7 of the state's norm.
+        // against 46 us). The halves' error is not larger (measured where the
+        // padding is laid out).
         return g_k6_kernel == 2 && n >= 11 && (k == 5 || beyond_caches(n, false)) ? LAYOUT_SPLIT16F : LAYOUT_MFMA32F;
     }
     const int nb = (k == 6) ? 1 : 2;
