@@ -74,6 +74,9 @@ def kernel_name(rec, k6_kernel=2, pair_tile=11, dbl=False, n=None) -> str:
     if not rec.get("mfma"):
         return "k_cluster_valu<float, %d>" % k
     if k == 7:  # the direct kernel only; its second flag sums the reductions
+        if n is not None:
+            return "k_cluster_f32_split7<%s, %s, %s>" % (b(lowt), b(rec.get("stats")),
+                                                         b(far and first(1, 4) and not rec.get("stats")))
         return "k_cluster_f32_split7<%s, %s>" % (b(lowt), b(rec.get("stats")))
     if n is not None and k6_kernel == 2 and (k == 6 or k == 5 and n >= 11 or k == 4 and far):
         # 4 and 5 qubits are padded to 6, with qubits above the lowest five others

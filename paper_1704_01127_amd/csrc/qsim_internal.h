@@ -112,6 +112,10 @@ struct BuildOp {
     int64_t out_off;    // byte offset of the output inside the matrix region
 };
 
+// The tile counters of a 7-qubit pass (8, 128 bytes apart) lie behind its
+// matrix: a slot holds the real-split size, twice the halves.
+constexpr int64_t kTicketOff7 = 4 * 128 * 128 * 2;
+
 // Geometry of one cluster application.
 struct ClusterGeom {
     int32_t t[kMaxK];   // target qubits: bit j of the matrix index is qubit t[j]

@@ -918,11 +918,12 @@ __device__ __forceinline__ ColFactor<float> epi_combine(uint32_t tb, double tr, 
 // amplitude (8 s + i) | h << 6); result register r of row block rb holds its
 // amplitude j = 16 rb + r (physical row 8 (r / 4) + 4 h + r % 4). The builder
 // permutes M once to match (LAYOUT_SPLIT7).
-template <bool LOWT, bool STATS = false>
+template <bool LOWT, bool STATS = false, bool NT = false>
 __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restrict__ psi,
                                                                const half8* __restrict__ Ap,
                                                                const EpiDesc* __restrict__ epi,
-                                                               ClusterGeom g, double* __restrict__ part) {
+                                                               ClusterGeom g, double* __restrict__ part,
+                                                               uint32_t* __restrict__ tickets) {
     constexpr int K = 7, HX = 64, RB = 4, S = 8, NP = RB * S * 64;
     // parts: 16 Re M hi, lo, 16 Im M hi, lo; entry (rb, s, lane) of each
     __shared__ half8 L[4 * NP];
@@ -947,7 +948,20 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
     const uint64_t cown = PAIR ? (uint64_t)((p >> 4) & 1) : 0;  // the lane's own column: cpair + cown
     const uint64_t roff = cown ? (uint64_t(1) << g.t[0]) : 0;   // odd rows
     const uint64_t ntiles = g.ncols / 32;
-    const uint64_t stride = (uint64_t)gridDim.x * 4;
+    // Beyond the caches tiles are handed out in order, by one counter per XCD for
+    // its own eighth of the state, so that the waves, which drift apart, still
+    // work on one compact stretch per XCD (30 qubits, 23 target sets: 3.45 ms per
+    // pass against 3.55 ms with a fixed stride, 3.74 ms without non-temporal
+    // accesses as well); smaller states take a fixed stride (20 qubits: the
+    // counters cost 0.7 us).
+    const bool dealt = tickets != nullptr;
+    const uint32_t mine = dealt ? blockIdx.x & 7 : 0u;
+    const uint32_t nmine = (uint32_t)(dealt ? ntiles / 8 : ntiles);
+    const uint64_t tile0 = (uint64_t)mine * nmine;
+    const uint32_t stride = gridDim.x * 4;
+    auto take = [&](uint32_t fixed) -> uint32_t {  // the next tile's number (dealt: in lane 0)
+        return dealt ? (lane == 0 ? atomicAdd(tickets + mine * 32, 1u) : 0u) : fixed;
+    };
     const bool has_epi = epi != nullptr;
     const bool has_ph = has_epi && epi->n_ph > 0;
     // state offset of the lane's amplitude j = 8 a + i: olo[i] | ohi[a] (bits of
@@ -960,13 +974,13 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
                  ((i & 4) ? uint64_t(1) << g.t[5] : 0);
     }
 
-    uint64_t tile = (uint64_t)xcd_block() * 4 + (threadIdx.x >> 6);
+    uint32_t cur = __builtin_amdgcn_readfirstlane(take(xcd_block() * 4 + (threadIdx.x >> 6)));
     double sv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (tile >= ntiles) {  // uniform in the wave: every wave reaches one reduction
+    if (cur >= nmine) {  // uniform in the wave: every wave reaches one reduction
         if constexpr (STATS) block_reduce_store(sv, 3, 0u, part + blockIdx.x * 8);
         return;
     }
-    const uint64_t last = ntiles - 1;
+    uint32_t ahead = take(cur + stride);
     // amplitudes 8 a .. 8 a + 7 of the lane for a in [A0, A1)
     // (the bits are disjoint, so the OR is a sum: one pointer per group a,
     // then the low offsets added to it)
@@ -979,7 +993,7 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
             if (LOWT || PAIR) {
 #pragma unroll
                 for (int i = 0; i < 8; i += 2) {
-                    const float4 v = *reinterpret_cast<const float4*>(pa + olo[i]);
+                    const vf4 v = load16<NT>(reinterpret_cast<const vf4*>(pa + olo[i]));
                     const int j = 8 * a + i;
                     X[2 * j] = v.x; X[2 * j + 1] = v.y; X[2 * j + 2] = v.z; X[2 * j + 3] = v.w;
                 }
@@ -1067,7 +1081,7 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
         }
     };
 
-    uint64_t base = deposit_cols<K>(tile * 32 + cpair, g);
+    uint64_t base = deposit_cols<K>((tile0 + cur) * 32 + cpair, g);
     float unscale;
     {
         float B[2 * HX];
@@ -1078,8 +1092,11 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
         unscale = split(B);
     }
     do {
-        const uint64_t nxt = tile + stride < last ? tile + stride : last;
-        const uint64_t basen = deposit_cols<K>(nxt * 32 + cpair, g);
+        // past the end the last tile is read again, so that every round has the
+        // same loads; the number after it is on its way meanwhile
+        const uint32_t nxt = __builtin_amdgcn_readfirstlane(ahead);
+        const uint64_t basen = deposit_cols<K>((tile0 + min(nxt, nmine - 1)) * 32 + cpair, g);
+        ahead = take(nxt + stride);
         // the next tile's loads go out in two halves: the second once the
         // first four steps have freed their operand registers
         float Bn[2 * HX];
@@ -1156,7 +1173,7 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
                     }
                     float2* pa = psi + (b0 | ohi[j >> 3]);
                     if (LOWT || PAIR) {
-                        *reinterpret_cast<float4*>(pa + olo[j & 7]) = make_float4(v[0], v[1], v[2], v[3]);
+                        store16<NT>(reinterpret_cast<vf4*>(pa + olo[j & 7]), vf4{v[0], v[1], v[2], v[3]});
                     } else {
                         pa[olo[j & 7]] = make_float2(v[0], v[1]);
                         pa[olo[(j + 1) & 7]] = make_float2(v[2], v[3]);
@@ -1174,8 +1191,8 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
         }
         base = basen;
         unscale = split(Bn);
-        tile += stride;
-    } while (tile < ntiles);
+        cur = nxt;
+    } while (cur < nmine);
     if constexpr (STATS) block_reduce_store(sv, 3, 0u, part + blockIdx.x * 8);
 }
 
@@ -3812,6 +3829,8 @@ __device__ __forceinline__ void build_matrix(const BuildOp& op, int part, const 
 #pragma unroll
                 for (int w = 0; w < 4; ++w) *reinterpret_cast<half4v*>(A + w * NP7 + at) = p[w];
             }
+            // the kernel's tile counters
+            if (part == 0 && threadIdx.x < 256) reinterpret_cast<uint32_t*>(out + kTicketOff7)[threadIdx.x] = 0u;
         }
     } else if (op.layout == LAYOUT_SPLIT16F) {
         // k = 5 or 6, fp16 halves of 16 x the real-split matrix for
@@ -4420,22 +4439,25 @@ hipError_t launch_cluster(void* psi, bool dbl, const ClusterGeom& g, const void*
     if (layout == LAYOUT_SPLIT7 && !dbl && g.k == 7 && g.n >= 12) {
         const uint64_t tiles = g.ncols / 32;
         const unsigned grid = grid_for(tiles, 4, kSplit7Grid);
+        // the tile counters behind the matrix, which its builder zeroes (a pass
+        // over a state this large has a full grid and a multiple of 8 tiles)
+        uint32_t* tickets = beyond_caches(g.n, false)
+                                ? reinterpret_cast<uint32_t*>(static_cast<char*>(const_cast<void*>(mat)) + kTicketOff7)
+                                : nullptr;
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (float2*)psi, (const half8*)mat, epi, g, stats_part,
+                               tickets);
+        };
         if (stats_part) {
             *stats_blocks = grid;
-            if (g.t[0] == 0)
-                hipLaunchKernelGGL((k_cluster_f32_split7<true, true>), dim3(grid), dim3(256), 0, st, (float2*)psi,
-                                   (const half8*)mat, epi, g, stats_part);
-            else
-                hipLaunchKernelGGL((k_cluster_f32_split7<false, true>), dim3(grid), dim3(256), 0, st,
-                                   (float2*)psi, (const half8*)mat, epi, g, stats_part);
+            g.t[0] == 0 ? go(k_cluster_f32_split7<true, true>) : go(k_cluster_f32_split7<false, true>);
             return hipGetLastError();
         }
+        const bool nt = beyond_caches(g.n, false) && whole_lines(g, 1, 4);
         if (g.t[0] == 0)
-            hipLaunchKernelGGL(k_cluster_f32_split7<true>, dim3(grid), dim3(256), 0, st, (float2*)psi,
-                               (const half8*)mat, epi, g, nullptr);
+            nt ? go(k_cluster_f32_split7<true, false, true>) : go(k_cluster_f32_split7<true>);
         else
-            hipLaunchKernelGGL(k_cluster_f32_split7<false>, dim3(grid), dim3(256), 0, st, (float2*)psi,
-                               (const half8*)mat, epi, g, nullptr);
+            nt ? go(k_cluster_f32_split7<false, false, true>) : go(k_cluster_f32_split7<false>);
         return hipGetLastError();
     }
     if (layout == LAYOUT_SPLIT16F && !dbl && g.k == 6 && variant == 1) {
