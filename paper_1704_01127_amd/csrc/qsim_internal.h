@@ -145,7 +145,7 @@ inline void set_geom(ClusterGeom& g, int n, int k, const int* t) {
 struct StageGeom {
     int32_t nt;          // tile bits (k + C)
     int32_t tb[16];      // their state-bit positions, ascending
-    int32_t tpos[6];     // tau bit of target m
+    int32_t tpos[kMaxK]; // tau bit of target m
     int32_t cpos[9];     // tau bit of column bit b
     int32_t swz[6];      // 6-qubit staged loop: LDS slot of tau = tau ^ (XOR of swz[i] over set bits 5 + i)
     uint64_t ioff[32];   // state offset of linear chunk i (tau = i << lane_bits ...)

@@ -2062,7 +2062,7 @@ template <bool LOWT, int FOLD = 0>
 __device__ __forceinline__ void split6s_tiles(g_float2* __restrict__ gpsi, const half8* Ah, const half8* Al, float2* L,
                                               c_epi* __restrict__ epi, const StageGeom& sg, uint64_t tile,
                                               uint64_t tile_end, uint64_t stride, const FoldIn* fin = nullptr) {
-    constexpr int K = 6, C = 5, NT = K + C, HX = 32, RB = 4, S = 8, NL = 16;
+    constexpr int K = 6, C = 5, TB = K + C, HX = 32, RB = 4, S = 8, NL = 16;
     // an opaque lane: what is derived from it is computed per call, not hoisted
     // into a caller's loop (the batch kernel's item loop) and kept live there
     int lane = threadIdx.x & 63;
@@ -2152,7 +2152,7 @@ __device__ __forceinline__ void split6s_tiles(g_float2* __restrict__ gpsi, const
         for (int i = 0; i < NL; ++i) R[i] = *reinterpret_cast<const g_vf4*>(gpsi + ((t0 | ioff(i)) | lane_off));
     };
     if constexpr (FOLD == 0) {
-        load_tile(tile_base<NT>(tile, sg));
+        load_tile(tile_base<TB>(tile, sg));
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0);
         __builtin_amdgcn_sched_barrier(0);
@@ -2173,7 +2173,7 @@ __device__ __forceinline__ void split6s_tiles(g_float2* __restrict__ gpsi, const
             // a column bit; the column-only factor of that epilogue joins the
             // output factor
             if ((it & 63) == 0) {
-                const uint64_t bj = tile_base<NT>(tile + (uint64_t)lane * stride, sg);  // past the end: unused
+                const uint64_t bj = tile_base<TB>(tile + (uint64_t)lane * stride, sg);  // past the end: unused
                 t1b = 0;
                 t2b = 0;
                 if (fin->epi1 != nullptr) t1b = epi_tile_part(fin->epi1, bj, colmask, t1r, t1i);
@@ -2265,7 +2265,7 @@ __device__ __forceinline__ void split6s_tiles(g_float2* __restrict__ gpsi, const
             if constexpr (FOLD == 0) {
                 const uint64_t nxt = tile + stride < last ? tile + stride : last;
                 __builtin_amdgcn_sched_barrier(0);
-                load_tile(tile_base<NT>(nxt, sg));
+                load_tile(tile_base<TB>(nxt, sg));
                 __builtin_amdgcn_sched_barrier(0);
             }
             floatx16 acc[RB];
@@ -2289,7 +2289,7 @@ __device__ __forceinline__ void split6s_tiles(g_float2* __restrict__ gpsi, const
 #pragma unroll
             for (int j = 0; j < 2 * HX; ++j) X[j] = acc[j / 16][j % 16] * unscale;
         }
-        const uint64_t tb0 = tile_base<NT>(tile, sg);
+        const uint64_t tb0 = tile_base<TB>(tile, sg);
         if (has_epi) {
             ColFactor<float> f{0u, 0u, 1.0f, 0.0f};
             if constexpr (FOLD != 0) {
@@ -2622,23 +2622,29 @@ __global__ __launch_bounds__(512, 1) void k_fold2t_f32(float2* __restrict__ psi,
 
 // Table form with a 7-qubit second cluster (the first has at most 7 qubits):
 // the write-only pass has no matrix in LDS, only the table (rows of 128
-// outputs), so two work-groups fit per compute unit. The lanes own the
-// amplitudes the 7-qubit cluster kernel's lanes do - lane (p, h) the
-// amplitudes j | h << 6 of column p - and store them the same way; each
-// output is summed from at most 4 table rows, weighted by w at the first
-// cluster's index, then takes both epilogues' column factors and the second
-// one's row signs.
+// outputs). The lanes own the amplitudes the 7-qubit cluster kernel's lanes do
+// - lane (p, h) the amplitudes j | h << 6 of column p; each output is summed
+// from at most 4 table rows, weighted by w at the first cluster's index, then
+// takes both epilogues' column factors and the second one's row signs.
+//
+// The pass is bound by its stores. Those of the lanes' own order scatter over
+// partial 128-byte lines when the targets are low bits (at 30 qubits 2.71 ms
+// with targets 0-3 and 7-9, 1.70 ms with 0, 1, 6, 7, 12, 13, 19). So each wave
+// turns its tile round in LDS, a quarter at a time (the tile less targets 4
+// and 5: 8 KiB; a whole tile a wave would leave room for only 4 waves), and
+// stores 16 bytes a lane in state order: 1.62 and 1.58 ms (a plain
+// fill takes 1.25). Non-temporal stores gained nothing here (1.72 and 1.65).
 constexpr int kFold7Row = 130;  // LDS row: 128 outputs and a 16-byte pad
 
-template <bool LOWT>
-__global__ __launch_bounds__(256, 2) void k_fold2t7_f32(float2* __restrict__ psi, const float2* __restrict__ Yg,
+__global__ __launch_bounds__(512, 1) void k_fold2t7_f32(float2* __restrict__ psi, const float2* __restrict__ Yg,
                                                         const EpiDesc* __restrict__ epi2,
                                                         const EpiDesc* __restrict__ epi1, ClusterGeom g, Fold2Args f,
-                                                        FoldTabArgs a) {
-    constexpr int K = 7, HX = 64;
+                                                        FoldTabArgs a, StageGeom sg) {
+    constexpr int K = 7, HX = 64, WAVES = 8;
     __shared__ float2 Y[kFoldTab7Rows * kFold7Row];
     __shared__ float2 W[128];
     __shared__ int Wc[128];
+    __shared__ vf4 Ls[WAVES][512];
     const int no = __popc(a.omask);
     const int nq = 64 << (no + __popc(a.rmask));  // 16-byte pieces of the table
     for (int i = (int)threadIdx.x; i < nq; i += (int)blockDim.x)
@@ -2667,17 +2673,38 @@ __global__ __launch_bounds__(256, 2) void k_fold2t7_f32(float2* __restrict__ psi
     const int nsp = 1 << no;
 
     const int lane = threadIdx.x & 63, p = lane & 31, h = lane >> 5;
-    const uint64_t hoff = h ? (uint64_t(1) << g.t[K - 1]) : 0;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t ntiles = g.ncols / 32;
-    const uint64_t stride = (uint64_t)gridDim.x * 4;
-    uint64_t olo[8], ohi[8];
+    const uint64_t stride = (uint64_t)gridDim.x * WAVES;
+    // the quarter in LDS: the tile without the bits of targets 4 and 5
+    vf4* L4 = Ls[w];
+    float2* L2 = reinterpret_cast<float2*>(L4);
+    auto slot = [](int v) { return v ^ (((v >> 5) & 15) << 1); };  // upper bits folded into the bank bits
+    const int x4 = sg.tpos[4], x5 = sg.tpos[5];
+    auto sub = [&](int b) { return b - (b > x4) - (b > x5); };  // position of tile bit b in it
+    int ct = h << sub(sg.tpos[6]);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        olo[i] = target_off<3>(i, g);
-        ohi[i] = ((i & 1) ? uint64_t(1) << g.t[3] : 0) | ((i & 2) ? uint64_t(1) << g.t[4] : 0) |
-                 ((i & 4) ? uint64_t(1) << g.t[5] : 0);
+    for (int b = 0; b < 5; ++b)
+        if ((p >> b) & 1) ct |= 1 << sub(sg.cpos[b]);
+    const int lslot = slot(ct), lin = slot(2 * lane);
+    int rmask[4], cmask[3];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) rmask[m] = slot(1 << sub(sg.tpos[m]));
+#pragma unroll
+    for (int b = 0; b < 3; ++b) cmask[b] = slot(128 << b);
+    uint64_t lane_off = 0, imask[3] = {0, 0, 0};  // state offsets of its linear order
+#pragma unroll
+    for (int b = 0; b < 12; ++b) {
+        if (b == x4 || b == x5) continue;
+        const int at = sub(b);
+        const uint64_t bit = uint64_t(1) << sg.tb[b];
+        if (at >= 1 && at <= 6 && ((lane >> (at - 1)) & 1)) lane_off |= bit;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (at == 7 + c) imask[c] = bit;
     }
-    for (uint64_t tile = (uint64_t)xcd_block() * 4 + (threadIdx.x >> 6); tile < ntiles; tile += stride) {
+    for (uint64_t tile = (uint64_t)xcd_block() * WAVES + w; tile < ntiles; tile += stride) {
+        const uint64_t tb0 = deposit_cols<K>(tile * 32, g);
         const uint64_t base = deposit_cols<K>(tile * 32 + p, g);
         // the first cluster's index from the column's bits (its qubits among
         // the second's targets are rows: zero in base)
@@ -2717,24 +2744,35 @@ __global__ __launch_bounds__(256, 2) void k_fold2t7_f32(float2* __restrict__ psi
             uci = -uci;
         }
         const uint32_t wl = f2.w & 63u;
-        const uint64_t b0 = base | hoff;
 #pragma unroll
-        for (int j = 0; j < HX; j += 2) {
-            float v[4];
+        for (int qt = 0; qt < 4; ++qt) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const float xr = X[2 * (j + u)], xi = X[2 * (j + u) + 1];
-                const float neg = (__popc((uint32_t)(j + u) & wl) & 1) ? -1.0f : 1.0f;
-                v[2 * u] = neg * fmaf(xr, ucr, -(xi * uci));
-                v[2 * u + 1] = neg * fmaf(xr, uci, xi * ucr);
+            for (int r = 0; r < 16; ++r) {
+                const int j = 16 * qt + r;
+                const float xr = X[2 * j], xi = X[2 * j + 1];
+                const float neg = (__popc((uint32_t)j & wl) & 1) ? -1.0f : 1.0f;
+                int at = lslot;
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    if ((r >> m) & 1) at ^= rmask[m];
+                L2[at] = make_float2(neg * fmaf(xr, ucr, -(xi * uci)), neg * fmaf(xr, uci, xi * ucr));
             }
-            float2* pa = psi + (b0 | ohi[j >> 3]);
-            if (LOWT) {
-                *reinterpret_cast<float4*>(pa + olo[j & 7]) = make_float4(v[0], v[1], v[2], v[3]);
-            } else {
-                pa[olo[j & 7]] = make_float2(v[0], v[1]);
-                pa[olo[(j + 1) & 7]] = make_float2(v[2], v[3]);
+            wave_lds_fence();
+            vf4* out = reinterpret_cast<vf4*>(psi + (tb0 | ((qt & 1) ? uint64_t(1) << g.t[4] : 0) |
+                                                     ((qt & 2) ? uint64_t(1) << g.t[5] : 0) | lane_off));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                int at = lin;
+                uint64_t o = 0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if ((i >> c) & 1) {
+                        at ^= cmask[c];
+                        o |= imask[c];
+                    }
+                out[o >> 1] = L4[at >> 1];
             }
+            wave_lds_fence();
         }
     }
 }
@@ -4163,30 +4201,24 @@ hipError_t launch_fold2(void* psi, const ClusterGeom& g2, const void* mat2, cons
         a.rmask = rmask;
         if (g2.k == 7) {
             hipLaunchKernelGGL(k_fold2_table<7>, dim3(1u << (no + nr)), dim3(128), 0, st, (float2*)table, a);
-            const unsigned grid7 = grid_for(g2.ncols / 32, 4, 2 * kSplit7Grid);
-            if (g2.t[0] == 0)
-                hipLaunchKernelGGL(k_fold2t7_f32<true>, dim3(grid7), dim3(256), 0, st, (float2*)psi,
-                                   (const float2*)table, epi2, epi1, g2, f, a);
-            else
-                hipLaunchKernelGGL(k_fold2t7_f32<false>, dim3(grid7), dim3(256), 0, st, (float2*)psi,
-                                   (const float2*)table, epi2, epi1, g2, f, a);
+            const unsigned grid7 = grid_for(g2.ncols / 32, 8, kSplit7Grid);
+            hipLaunchKernelGGL(k_fold2t7_f32, dim3(grid7), dim3(512), 0, st, (float2*)psi, (const float2*)table, epi2,
+                               epi1, g2, f, a, sg);
             return hipGetLastError();
         }
         hipLaunchKernelGGL(k_fold2_table<6>, dim3(1u << (no + nr)), dim3(64), 0, st, (float2*)table, a);
-        if (g2.t[0] == 0)
-            hipLaunchKernelGGL(k_fold2t_f32<true>, dim3(grid), dim3(512), 0, st, (float2*)psi, (const float2*)table,
-                               epi2, epi1, sg, f, a, tiles);
-        else
-            hipLaunchKernelGGL(k_fold2t_f32<false>, dim3(grid), dim3(512), 0, st, (float2*)psi,
-                               (const float2*)table, epi2, epi1, sg, f, a, tiles);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, st, (float2*)psi, (const float2*)table, epi2, epi1, sg,
+                               f, a, tiles);
+        };
+        g2.t[0] == 0 ? go(k_fold2t_f32<true>) : go(k_fold2t_f32<false>);
         return hipGetLastError();
     }
-    if (g2.t[0] == 0)
-        hipLaunchKernelGGL(k_fold2_f32<true>, dim3(grid), dim3(512), 0, st, (float2*)psi, (const half8*)mat2, epi2,
-                           epi1, sg, f, tiles);
-    else
-        hipLaunchKernelGGL(k_fold2_f32<false>, dim3(grid), dim3(512), 0, st, (float2*)psi, (const half8*)mat2, epi2,
-                           epi1, sg, f, tiles);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, st, (float2*)psi, (const half8*)mat2, epi2, epi1, sg, f,
+                           tiles);
+    };
+    g2.t[0] == 0 ? go(k_fold2_f32<true>) : go(k_fold2_f32<false>);
     return hipGetLastError();
 }
 
