@@ -3996,85 +3996,120 @@ __device__ void block_reduce_store(double (&vals)[8], int nv, unsigned maxmask, 
     }
 }
 
-// The grid-stride loops below are unrolled by kRedU with all loads of a
-// round issued before any arithmetic: with one load in flight per lane the
-// reductions were bound by memory latency, not bandwidth. Every load
-// instruction stays coalesced (lane l reads element i + l, round after round).
-constexpr int kRedU = 8;
+// The streaming reductions are bound by HBM. A work-group takes runs of U * 256
+// consecutive units (W amplitudes: 16 bytes a lane, where the pointers are so
+// aligned) and issues all of a run's loads before any arithmetic: a run is one
+// stretch of pages and channels, where a grid-wide stride between a lane's
+// loads touched U windows 4 MiB apart. Beyond the caches the accesses are
+// non-temporal. At 27 qubits, fp32: k_stats with probabilities 318 -> 275 us
+// (5.9 TB/s), k_compare 440 -> 306 us (7.0 TB/s).
+template <typename T, int W>
+struct AmpUnit {
+    typedef T type __attribute__((ext_vector_type(2 * W)));
+};
+template <typename P, int W>
+struct ProbUnit {
+    typedef P type __attribute__((ext_vector_type(W)));
+};
+template <typename P>
+struct ProbUnit<P, 1> {
+    typedef P type;
+};
 
-template <typename T, typename P>
-__global__ __launch_bounds__(256) void k_stats(const typename Cplx<T>::type* __restrict__ psi, uint64_t count,
-                                               P* __restrict__ probs, double* __restrict__ part) {
-    using V = typename Cplx<T>::type;
+template <typename T, typename P, int W, int U, bool NT>
+__global__ __launch_bounds__(256) void k_stats(const void* __restrict__ psi, uint64_t units, void* __restrict__ probs,
+                                               double* __restrict__ part) {
+    using V = typename AmpUnit<T, W>::type;
+    using Q = typename ProbUnit<P, W>::type;
+    const V* in = reinterpret_cast<const V*>(psi);
+    Q* out = reinterpret_cast<Q*>(probs);
     double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
     auto acc = [&](const V& a, uint64_t i) {
-        const double pr = (double)a.x * (double)a.x + (double)a.y * (double)a.y;
-        if constexpr (sizeof(T) == 4) {
-            stats_acc_f(v, a.x, a.y);
-        } else {
-            v[0] += pr;
-            v[1] += pr * pr;
-            if (pr > 0.0) v[2] -= pr * log(pr);
+        Q q;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const T x = a[2 * w], y = a[2 * w + 1];
+            const double pr = (double)x * (double)x + (double)y * (double)y;
+            if constexpr (sizeof(T) == 4) {
+                stats_acc_f(v, x, y);
+            } else {
+                v[0] += pr;
+                v[1] += pr * pr;
+                if (pr > 0.0) v[2] -= pr * log(pr);
+            }
+            if constexpr (W == 1)
+                q = (P)pr;
+            else
+                q[w] = (P)pr;
         }
-        if (probs) probs[i] = (P)pr;
+        if (out) store16<NT>(out + i, q);
     };
-    uint64_t i = (uint64_t)xcd_block() * 256 + threadIdx.x;  // any bijection: partials stay per work-group
-    for (; i + (kRedU - 1) * stride < count; i += kRedU * stride) {
-        V a[kRedU];
+    const uint64_t step = (uint64_t)gridDim.x * U * 256;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * U * 256 + threadIdx.x; i0 < units; i0 += step) {
+        V a[U];  // units is a multiple of U * 256, or U is 1
 #pragma unroll
-        for (int u = 0; u < kRedU; ++u) a[u] = psi[i + u * stride];
+        for (int u = 0; u < U; ++u) a[u] = load16<NT>(in + i0 + u * 256);
 #pragma unroll
-        for (int u = 0; u < kRedU; ++u) acc(a[u], i + u * stride);
+        for (int u = 0; u < U; ++u) acc(a[u], i0 + u * 256);
     }
-    for (; i < count; i += stride) acc(psi[i], i);
     block_reduce_store(v, 3, 0u, part + blockIdx.x * 8);
 }
 
-template <typename T, typename R>
-__global__ __launch_bounds__(256) void k_compare(const typename Cplx<T>::type* __restrict__ psi,
-                                                 const typename Cplx<R>::type* __restrict__ ref, uint64_t count,
-                                                 double* __restrict__ part) {
-    using V = typename Cplx<T>::type;
-    using W = typename Cplx<R>::type;
+template <typename T, typename R, int W, int U, bool NT>
+__global__ __launch_bounds__(256) void k_compare(const void* __restrict__ psi, const void* __restrict__ ref,
+                                                 uint64_t units, double* __restrict__ part) {
+    using V = typename AmpUnit<T, W>::type;
+    using X = typename AmpUnit<R, W>::type;
+    const V* pa = reinterpret_cast<const V*>(psi);
+    const X* pr = reinterpret_cast<const X*>(ref);
     double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
-    auto acc = [&](const V& a, const W& r) {
-        const double ar = a.x, ai = a.y, rr = r.x, ri = r.y;
-        v[0] += rr * ar + ri * ai;  // Re <ref|psi>
-        v[1] += rr * ai - ri * ar;  // Im <ref|psi>
-        v[2] += rr * rr + ri * ri;
-        v[3] += ar * ar + ai * ai;
-        const double dr = ar - rr, di = ai - ri;
-        v[4] = fmax(v[4], sqrt(dr * dr + di * di));
-    };
-    uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    constexpr int U = kRedU / 2;
-    for (; i + (U - 1) * stride < count; i += U * stride) {
+    const uint64_t step = (uint64_t)gridDim.x * U * 256;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * U * 256 + threadIdx.x; i0 < units; i0 += step) {
         V a[U];
-        W r[U];
+        X r[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            a[u] = psi[i + u * stride];
-            r[u] = ref[i + u * stride];
+            a[u] = load16<NT>(pa + i0 + u * 256);
+            r[u] = load16<NT>(pr + i0 + u * 256);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc(a[u], r[u]);
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const double ar = a[u][2 * w], ai = a[u][2 * w + 1], rr = r[u][2 * w], ri = r[u][2 * w + 1];
+                v[0] += rr * ar + ri * ai;  // Re <ref|psi>
+                v[1] += rr * ai - ri * ar;  // Im <ref|psi>
+                v[2] += rr * rr + ri * ri;
+                v[3] += ar * ar + ai * ai;
+                const double dr = ar - rr, di = ai - ri;
+                v[4] = fmax(v[4], dr * dr + di * di);
+            }
     }
-    for (; i < count; i += stride) acc(psi[i], ref[i]);
+    v[4] = sqrt(v[4]);  // the root is monotone: the same value as the largest root
     block_reduce_store(v, 5, 1u << 4, part + blockIdx.x * 8);
 }
 
-// Sum (or max) the per-block partials in a fixed order: deterministic.
-__global__ __launch_bounds__(256) void k_reduce_final(const double* __restrict__ part, int nblocks, int nv,
-                                                      unsigned maxmask, double* __restrict__ res) {
+// Sum (or max) the per-block partials in a fixed order: deterministic. One
+// work-group, bound by latency: eight rows of partials a thread in flight.
+template <int NV, unsigned MAXMASK>
+__global__ __launch_bounds__(256) void k_reduce_final(const double* __restrict__ part, int nblocks,
+                                                      double* __restrict__ res) {
+    constexpr int R = kReduceBlocks / 256;
     double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nblocks; b += 256)
-        for (int i = 0; i < nv; ++i) {
-            const double x = part[b * 8 + i];
-            v[i] = ((maxmask >> i) & 1) ? fmax(v[i], x) : v[i] + x;
+    for (int b0 = threadIdx.x; b0 < nblocks; b0 += R * 256) {
+        double x[R][NV];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int b = b0 + 256 * r;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) x[r][i] = b < nblocks ? part[b * 8 + i] : 0.0;
         }
-    block_reduce_store(v, nv, maxmask, res);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) v[i] = ((MAXMASK >> i) & 1) ? fmax(v[i], x[r][i]) : v[i] + x[r][i];
+    }
+    block_reduce_store(v, NV, MAXMASK, res);
 }
 
 // ------------------------------------------------------------ launchers
@@ -4090,6 +4125,10 @@ inline unsigned tile_grid(uint64_t tiles) { return (unsigned)((tiles + 3) / 4); 
 // tile is on the lanes, so no such target may be among the line's `bits` bits.
 inline bool whole_lines(const ClusterGeom& g, int first, int bits) { return g.t[first] >= bits; }
 constexpr unsigned kStreamGrid = 8192;  // blocks of 256 threads for grid-stride streaming kernels
+// Streaming reductions: runs of rounds from this many work-groups up, single
+// rounds below (one fp32 call at 20 qubits, 256 work-groups of runs or 2048 of
+// single rounds: 27.7 or 31.0 us; at 18 qubits, 64 or 512: 27.0 both ways).
+constexpr unsigned kDeepBlocks = 64;
 constexpr unsigned kPersistGrid = 2048; // work-groups of the persistent cluster kernels
 constexpr unsigned kPairGrid = 256;     // one 12-wave work-group per compute unit (LDS-limited)
 constexpr unsigned kStagedGrid = 256;   // one 8-wave work-group per compute unit (LDS-limited)
@@ -4642,26 +4681,59 @@ hipError_t launch_cz(void* psi, bool dbl, int n, int a, int b, hipStream_t st) {
                : launch_phase_t<float, true>(psi, n, a, b, 0, 0, st);
 }
 
+namespace {
+// Launch of a streaming reduction over `units` (a power of two): runs of U
+// rounds where they still fill the chip, else single rounds.
+template <typename F>
+unsigned launch_stream(uint64_t units, bool nt, F&& go) {
+    constexpr int U = 8;
+    const bool deep = units >= uint64_t(U) * 256 * kDeepBlocks;
+    const unsigned grid = grid_for(units, deep ? U * 256 : 256, kReduceBlocks);
+    if (!deep)
+        go(grid, std::integral_constant<int, 1>{}, std::false_type{});
+    else if (nt)
+        go(grid, std::integral_constant<int, U>{}, std::true_type{});
+    else
+        go(grid, std::integral_constant<int, U>{}, std::false_type{});
+    return grid;
+}
+inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
+
+template <typename T, typename P, int W>
+void launch_stats_t(const void* psi, int n, void* probs, double* part, double* res, hipStream_t st) {
+    const uint64_t units = (uint64_t(1) << n) / W;
+    const unsigned grid = launch_stream(units, beyond_caches(n, sizeof(T) == 8), [&](unsigned g, auto u, auto nt) {
+        hipLaunchKernelGGL((k_stats<T, P, W, decltype(u)::value, decltype(nt)::value>), dim3(g), dim3(256), 0, st, psi,
+                           units, probs, part);
+    });
+    hipLaunchKernelGGL((k_reduce_final<3, 0u>), dim3(1), dim3(256), 0, st, part, (int)grid, res);
+}
+
+template <typename T, typename R, int W>
+void launch_compare_t(const void* psi, int n, const void* ref, double* part, double* res, hipStream_t st) {
+    const uint64_t units = (uint64_t(1) << n) / W;
+    const unsigned grid = launch_stream(units, beyond_caches(n, sizeof(T) == 8), [&](unsigned g, auto u, auto nt) {
+        hipLaunchKernelGGL((k_compare<T, R, W, decltype(u)::value, decltype(nt)::value>), dim3(g), dim3(256), 0, st,
+                           psi, ref, units, part);
+    });
+    hipLaunchKernelGGL((k_reduce_final<5, 1u << 4>), dim3(1), dim3(256), 0, st, part, (int)grid, res);
+}
+}  // namespace
+
+// Two complex64 amplitudes a lane where every pointer allows 16-byte accesses
+// (8 bytes for the fp32 probabilities): a state may be a caller's view.
 hipError_t launch_stats(const void* psi, bool dbl, int n, void* probs, bool probs_dbl, double* part,
                         double* res, hipStream_t st) {
-    const uint64_t cnt = uint64_t(1) << n;
-    const unsigned grid = grid_for(cnt, 256, kReduceBlocks);
-    if (dbl) {
-        if (probs_dbl)
-            hipLaunchKernelGGL((k_stats<double, double>), dim3(grid), dim3(256), 0, st, (const double2*)psi, cnt,
-                               (double*)probs, part);
-        else
-            hipLaunchKernelGGL((k_stats<double, float>), dim3(grid), dim3(256), 0, st, (const double2*)psi, cnt,
-                               (float*)probs, part);
-    } else {
-        if (probs_dbl)
-            hipLaunchKernelGGL((k_stats<float, double>), dim3(grid), dim3(256), 0, st, (const float2*)psi, cnt,
-                               (double*)probs, part);
-        else
-            hipLaunchKernelGGL((k_stats<float, float>), dim3(grid), dim3(256), 0, st, (const float2*)psi, cnt,
-                               (float*)probs, part);
-    }
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, st, part, (int)grid, 3, 0u, res);
+    const bool wide = aligned(psi, 16) && aligned(probs, probs_dbl ? 16 : 8);
+    if (dbl)
+        probs_dbl ? launch_stats_t<double, double, 1>(psi, n, probs, part, res, st)
+                  : launch_stats_t<double, float, 1>(psi, n, probs, part, res, st);
+    else if (wide)
+        probs_dbl ? launch_stats_t<float, double, 2>(psi, n, probs, part, res, st)
+                  : launch_stats_t<float, float, 2>(psi, n, probs, part, res, st);
+    else
+        probs_dbl ? launch_stats_t<float, double, 1>(psi, n, probs, part, res, st)
+                  : launch_stats_t<float, float, 1>(psi, n, probs, part, res, st);
     return hipGetLastError();
 }
 
@@ -4767,30 +4839,22 @@ hipError_t launch_permute(void* psi, bool dbl, int n, const PermGeom& pg, hipStr
 }
 
 hipError_t launch_reduce_stats(const double* part, unsigned nblocks, double* res, hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, st, part, (int)nblocks, 3, 0u, res);
+    hipLaunchKernelGGL((k_reduce_final<3, 0u>), dim3(1), dim3(256), 0, st, part, (int)nblocks, res);
     return hipGetLastError();
 }
 
 hipError_t launch_compare(const void* psi, bool dbl, int n, const void* ref, bool ref_dbl, double* part,
                           double* res, hipStream_t st) {
-    const uint64_t cnt = uint64_t(1) << n;
-    const unsigned grid = grid_for(cnt, 256, kReduceBlocks);
-    if (dbl) {
-        if (ref_dbl)
-            hipLaunchKernelGGL((k_compare<double, double>), dim3(grid), dim3(256), 0, st, (const double2*)psi,
-                               (const double2*)ref, cnt, part);
-        else
-            hipLaunchKernelGGL((k_compare<double, float>), dim3(grid), dim3(256), 0, st, (const double2*)psi,
-                               (const float2*)ref, cnt, part);
-    } else {
-        if (ref_dbl)
-            hipLaunchKernelGGL((k_compare<float, double>), dim3(grid), dim3(256), 0, st, (const float2*)psi,
-                               (const double2*)ref, cnt, part);
-        else
-            hipLaunchKernelGGL((k_compare<float, float>), dim3(grid), dim3(256), 0, st, (const float2*)psi,
-                               (const float2*)ref, cnt, part);
-    }
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, st, part, (int)grid, 5, 1u << 4, res);
+    const bool wide = aligned(psi, 16) && aligned(ref, 16);
+    if (dbl)
+        ref_dbl ? launch_compare_t<double, double, 1>(psi, n, ref, part, res, st)
+                : launch_compare_t<double, float, 1>(psi, n, ref, part, res, st);
+    else if (ref_dbl)
+        launch_compare_t<float, double, 1>(psi, n, ref, part, res, st);
+    else if (wide)
+        launch_compare_t<float, float, 2>(psi, n, ref, part, res, st);
+    else
+        launch_compare_t<float, float, 1>(psi, n, ref, part, res, st);
     return hipGetLastError();
 }
 
