@@ -85,13 +85,19 @@ class TaskPool {
         if (fs.empty()) return;
         auto b = std::make_shared<Batch>();
         b->n = (int)fs.size();
+        b->left = b->n;
         b->fs = std::move(fs);
         {
             std::lock_guard<std::mutex> l(m_);
             q_.push_back(b);
         }
-        cv_.notify_all();
+        // one worker per task left over for them: waking all of them only has
+        // them queue for the mutex
+        for (int i = 1; i < b->n; ++i) cv_.notify_one();
         work(*b);
+        // the last tasks end within microseconds of this thread's own, sooner
+        // than a sleeping thread wakes
+        for (int i = 0; i < 2000 && b->left.load() > 0; ++i) std::this_thread::yield();
         std::unique_lock<std::mutex> l(b->m);
         b->cv.wait(l, [&] { return b->done == b->n; });
         if (b->error) std::rethrow_exception(b->error);
@@ -102,6 +108,7 @@ class TaskPool {
         std::vector<std::function<void()>> fs;
         int n = 0;
         std::atomic<int> next{0};
+        std::atomic<int> left{0};
         std::mutex m;
         std::condition_variable cv;
         int done = 0;  // under m
@@ -128,6 +135,7 @@ class TaskPool {
             std::lock_guard<std::mutex> l(b.m);
             if (e && !b.error) b.error = e;
             if (++b.done == b.n) b.cv.notify_all();
+            b.left.fetch_sub(1);
         }
     }
     explicit TaskPool(int workers) {
@@ -153,6 +161,12 @@ class TaskPool {
     std::deque<std::shared_ptr<Batch>> q_;
 };
 
+// Below this many gates to place, over all candidates, handing them to the
+// pool takes longer than building them here (12 qubits, depth 16, 3 candidates
+// of 76 gates: 32 us on the pool, 24 on one thread; 20 qubits, depth 25, 3 of
+// 221: 101 and 133).
+constexpr size_t kPoolGates = 400;
+
 // Results of the tasks, in order: on the pool when parallel, else one after
 // another on this thread. Only tasks with want[i] (all when want is null) run.
 // On the pool they start by descending first_key[i] (longest expected first,
@@ -177,178 +191,211 @@ std::vector<T> run_tasks(bool parallel, const std::vector<std::function<T()>>& f
     return out;
 }
 
+// The gates of a schedule on flat arrays, built once for all its candidates.
+// The queue of qubit q (its gates in program order) is items[first[q]...],
+// ended by an item without a gate; the head of a queue is a position in items.
+// An item holds what the searches ask of its gate, so that walking a queue
+// stays within it: a gate of two qubits is ready when the head of the other
+// one's queue is at `need`.
 struct Dag {
+    struct Item {
+        uint64_t mask;  // the gate's qubits
+        int gi;         // gate index, -1: end of the queue
+        int need;       // position of the gate in the other qubit's queue (1 qubit: this position)
+        uint8_t other;  // the other qubit (1 qubit: this one)
+        uint8_t nq;
+        bool diag, cz;
+    };
     int n;
-    const std::vector<SGate>* g;
-    std::vector<std::vector<int>> queue;  // per qubit, gate indices in program order
-    std::vector<uint64_t> mask;           // per gate, qubit bit mask
+    std::vector<Item> items;
+    int first[64];
+    const std::vector<SGate>& g;
+    std::vector<int> pos;  // per gate and qubit (kMaxGateQ each): position in that qubit's queue
 
-    bool ready(const std::vector<int>& head, int gi) const {
-        const SGate& s = (*g)[gi];
-        for (int j = 0; j < s.nq; ++j) {
-            const auto& qq = queue[s.q[j]];
-            const int h = head[s.q[j]];
-            if (h >= (int)qq.size() || qq[h] != gi) return false;
+    Dag(int n_, const std::vector<SGate>& gates, const std::vector<char>& dropped)
+        : n(n_), g(gates), pos(gates.size() * kMaxGateQ) {
+        const int ng = (int)gates.size();
+        int len[64] = {};
+        for (int i = 0; i < ng; ++i)
+            if (!dropped[i])
+                for (int j = 0; j < gates[i].nq; ++j) ++len[gates[i].q[j]];
+        int total = 0, fill[64];
+        for (int q = 0; q < n; ++q) {
+            first[q] = fill[q] = total;
+            total += len[q] + 1;
         }
+        items.assign(total, Item{~uint64_t(0), -1, 0, 0, 0, false, false});
+        for (int i = 0; i < ng; ++i) {
+            if (dropped[i]) continue;
+            const SGate& x = gates[i];
+            Item it{0, i, 0, 0, (uint8_t)x.nq, x.diag, x.kind == G_CZ};
+            for (int j = 0; j < x.nq; ++j) {
+                it.mask |= uint64_t(1) << x.q[j];
+                pos[i * kMaxGateQ + j] = fill[x.q[j]]++;
+            }
+            for (int j = 0; j < x.nq; ++j) {
+                const int o = x.nq == 2 ? 1 - j : j;
+                it.other = (uint8_t)x.q[o];
+                it.need = pos[i * kMaxGateQ + o];
+                items[pos[i * kMaxGateQ + j]] = it;
+            }
+        }
+    }
+    // Is the gate of an item at the head of its queue ready?
+    bool ready(const int* head, const Item& x) const {
+        if (x.nq <= 2) return head[x.other] == x.need;
+        for (int j = 0; j < x.nq; ++j)
+            if (head[g[x.gi].q[j]] != pos[x.gi * kMaxGateQ + j]) return false;
         return true;
     }
-    void pop(std::vector<int>& head, int gi) const {
-        const SGate& s = (*g)[gi];
-        for (int j = 0; j < s.nq; ++j) head[s.q[j]]++;
+    // Take the gate of an item at the head of qubit q's queue.
+    void pop(int* head, const Item& x, int q) const {
+        if (x.nq <= 2) {
+            head[q]++;
+            if (x.nq == 2) head[x.other]++;
+            return;
+        }
+        for (int j = 0; j < x.nq; ++j) head[g[x.gi].q[j]]++;
     }
-    // Ready gates, ascending index.
-    void ready_list(const std::vector<int>& head, std::vector<int>& out) const {
+    // Items of the ready gates, by ascending gate index.
+    void ready_list(const int* head, std::vector<const Item*>& out) const {
         out.clear();
         for (int q = 0; q < n; ++q) {
-            if (head[q] >= (int)queue[q].size()) continue;
-            const int gi = queue[q][head[q]];
-            if (ready(head, gi)) out.push_back(gi);
+            const Item& x = items[head[q]];
+            if (x.gi >= 0 && __builtin_ctzll(x.mask) == q && ready(head, x)) out.push_back(&x);
         }
-        std::sort(out.begin(), out.end());
-        out.erase(std::unique(out.begin(), out.end()), out.end());
+        std::sort(out.begin(), out.end(), [](const Item* a, const Item* b) { return a->gi < b->gi; });
+    }
+    // Take the ready gates that `fits` and those that become ready, reached
+    // from the qubits in `pending`. Taking a gate never makes another one
+    // unready, so the result is the same in any order. Returns their qubits.
+    template <typename P, typename F>
+    uint64_t closure(int* head, uint64_t pending, P&& fits, F&& taken) const {
+        uint64_t used = 0;
+        while (pending) {
+            const int q = __builtin_ctzll(pending);
+            pending &= pending - 1;
+            for (;;) {
+                const Item& x = items[head[q]];
+                if (x.gi < 0 || !fits(x) || !ready(head, x)) break;
+                pop(head, x, q);
+                taken(x);
+                used |= x.mask;
+                pending |= x.mask & ~(uint64_t(1) << q);
+            }
+        }
+        return used;
     }
 };
 
 struct Grown {
     uint64_t Q = 0;
-    std::vector<int> members, epi;
-    std::vector<int> head;
+    std::vector<int> members, epi;  // in no particular order
+    int head[64];
     int n_gates() const { return (int)(members.size() + epi.size()); }
 };
 
-// Queue heads and ready list (ascending gate index) of one growth, on fixed
-// arrays: a state has at most 64 qubits, so at most 64 gates are ready, and
-// the many trial growths of a step need no heap memory.
-struct Frontier {
-    int head[64];
-    int rl[64];
-    int nrl = 0;
-};
-
-bool ready_at(const Dag& d, const int* head, int gi) {
-    const SGate& s = (*d.g)[gi];
-    for (int j = 0; j < s.nq; ++j) {
-        const auto& qq = d.queue[s.q[j]];
-        const int h = head[s.q[j]];
-        if (h >= (int)qq.size() || qq[h] != gi) return false;
-    }
-    return true;
-}
-
-// Take gate gi: advance the heads of its qubits and update the ready list:
-// gi leaves it, and only the new heads of gi's qubits can become ready.
-void take(const Dag& d, Frontier& f, int gi) {
-    const SGate& s = (*d.g)[gi];
-    for (int j = 0; j < s.nq; ++j) f.head[s.q[j]]++;
-    int* end = f.rl + f.nrl;
-    int* p = std::lower_bound(f.rl, end, gi);
-    std::memmove(p, p + 1, (end - p - 1) * sizeof(int));
-    --f.nrl;
-    for (int j = 0; j < s.nq; ++j) {
-        const auto& qq = d.queue[s.q[j]];
-        const int h = f.head[s.q[j]];
-        if (h >= (int)qq.size()) continue;
-        const int g2 = qq[h];
-        if (!ready_at(d, f.head, g2)) continue;
-        end = f.rl + f.nrl;
-        p = std::lower_bound(f.rl, end, g2);
-        if (p != end && *p == g2) continue;
-        std::memmove(p + 1, p, (end - p) * sizeof(int));
-        *p = g2;
-        ++f.nrl;
-    }
-}
-
-// Grow a cluster from `seed` with at most `kcap` qubits, starting at f0. With
-// `within` != 0 there is no seed (seed = -1) and the cluster is the closure
+// Grow a cluster from `seed` with at most `kcap` qubits, from the queue heads
+// head0 with the ready gates `rl`: repeatedly the ready gate that adds the
+// fewest new qubits (then the lowest index) joins the matrix. With
+// `within` != 0 there is no seed (null) and the cluster is the closure
 // of that qubit set: every gate that becomes ready and lies inside it joins
 // the matrix. Returns the number of gates taken (matrix and diagonal
-// epilogue); `out`, when given, receives the cluster.
-int grow(const Dag& d, const Frontier& f0, int seed, int kcap, bool fuse_diag, uint64_t within, Grown* out) {
-    const auto& G = *d.g;
-    Frontier f = f0;
+// epilogue); `qubits` and `out`, when given, receive the cluster's.
+//
+// Gates that add no qubit are taken as a closure. The others that may join
+// either head the queue of a cluster qubit or lie outside the cluster, where
+// no head has moved: those are the gates of `rl` clear of it.
+int grow(const Dag& d, const int* head0, const std::vector<const Dag::Item*>& rl, const Dag::Item* seed, int kcap,
+         bool fuse_diag, uint64_t within, uint64_t* qubits, Grown* out) {
+    int h[64];
+    std::copy(head0, head0 + d.n, h);
     uint64_t Q = 0;
-    int n_mat = 0, n_epi_cz = 0, n_epi_ph = 0;
-    if (seed >= 0) {
-        Q = d.mask[seed];
+    int n_mat = 0, n_epi = 0;
+    auto joined = [&](const Dag::Item& x) {
         ++n_mat;
-        if (out) out->members.push_back(seed);
-        take(d, f, seed);
-    }
-    for (;;) {
-        // a gate that joins the matrix: fewest new qubits, then lowest index
-        int best = -1, best_new = 1 << 30;
-        for (int i = 0; i < f.nrl; ++i) {
-            const int gi = f.rl[i];
-            const uint64_t m = d.mask[gi];
-            if (within ? (m & ~within) != 0 : popc(Q | m) > kcap) continue;
-            const int nw = popc(m & ~Q);
-            if (nw < best_new) {
-                best = gi;
-                best_new = nw;
-                if (nw == 0) break;  // nothing beats it, and later gates have higher indices
+        if (out) out->members.push_back(x.gi);
+    };
+    if (within) {
+        Q = d.closure(h, within, [&](const Dag::Item& x) { return !(x.mask & ~within); }, joined);
+    } else {
+        const Dag::Item* best = seed;
+        for (int room = kcap, best_new = seed->nq; best;) {
+            const uint64_t added = best->mask & ~Q;
+            Q |= added;
+            room -= best_new;
+            d.closure(h, added, [&](const Dag::Item& x) { return !(x.mask & ~Q); }, joined);
+            best = nullptr;
+            best_new = room + 1;
+            if (room <= 0) break;
+            auto offer = [&](const Dag::Item* x, int nw) {
+                if (nw < best_new || (best && nw == best_new && x->gi < best->gi)) {
+                    best = x;
+                    best_new = nw;
+                }
+            };
+            for (uint64_t m = Q; m; m &= m - 1) {
+                const Dag::Item* x = &d.items[h[__builtin_ctzll(m)]];
+                if (x->gi < 0 || !(x->mask & ~Q)) continue;  // at the end, or waiting for a gate inside
+                if (d.ready(h, *x)) offer(x, x->nq <= 2 ? 1 : popc(x->mask & ~Q));
+            }
+            for (const Dag::Item* x : rl) {
+                if (best && best_new == 1 && x->gi > best->gi) break;  // ascending: nothing better follows
+                if (!(x->mask & Q)) offer(x, x->nq);
             }
         }
-        if (best < 0) break;
-        ++n_mat;
-        if (out) out->members.push_back(best);
-        Q |= d.mask[best];
-        take(d, f, best);
     }
-    // nothing fits: attach ready diagonal gates, lowest index first. Their
-    // qubits are sealed, and every gate they make ready touches one, so no
-    // further matrix gate can join; a gate made ready has a higher index than
-    // the one taken, so one forward pass over the ready list finds them all.
+    // nothing fits: attach the ready diagonal gates, and those they make
+    // ready. Their qubits are sealed, and every gate they make ready touches
+    // one, so no further matrix gate can join.
     if (fuse_diag && n_mat > 0) {
-        for (int i = 0; i < f.nrl;) {
-            const int gi = f.rl[i];
-            const bool cz = G[gi].kind == G_CZ;
-            if (!G[gi].diag || (cz && n_epi_cz >= kEpiMax) || (!cz && n_epi_ph >= kEpiMax)) {
-                ++i;
-                continue;
+        int e[64], n_cz = 0, n_ph = 0;
+        std::copy(h, h + d.n, e);
+        auto attach = [&](const Dag::Item& x) {
+            x.cz ? ++n_cz : ++n_ph;
+            if (out) out->epi.push_back(x.gi);
+        };
+        const uint64_t all = d.n < 64 ? (uint64_t(1) << d.n) - 1 : ~uint64_t(0);
+        d.closure(e, all, [](const Dag::Item& x) { return x.diag; }, attach);
+        if (n_cz > kEpiMax || n_ph > kEpiMax) {  // more than an epilogue holds: the lowest indices of each kind
+            if (out) out->epi.clear();
+            n_cz = n_ph = 0;
+            std::copy(h, h + d.n, e);
+            for (;;) {
+                const Dag::Item* best = nullptr;
+                int at = 0;
+                for (int q = 0; q < d.n; ++q) {
+                    const Dag::Item& x = d.items[e[q]];
+                    if (x.gi < 0 || (best && x.gi >= best->gi)) continue;
+                    if (x.diag && (x.cz ? n_cz : n_ph) < kEpiMax && d.ready(e, x)) {
+                        best = &x;
+                        at = q;
+                    }
+                }
+                if (!best) break;
+                d.pop(e, *best, at);
+                attach(*best);
             }
-            if (out) out->epi.push_back(gi);
-            if (cz) ++n_epi_cz; else ++n_epi_ph;
-            take(d, f, gi);  // removes rl[i]; gates it makes ready sort after it
         }
+        n_epi = n_cz + n_ph;
+        std::copy(e, e + d.n, h);
     }
+    if (qubits) *qubits = Q;
     if (out) {
         out->Q = Q;
-        out->head.assign(f.head, f.head + d.n);
+        std::copy(h, h + d.n, out->head);
     }
-    return n_mat + n_epi_cz + n_epi_ph;
+    return n_mat + n_epi;
 }
 
-// Gates the closure of qubit set S takes into its matrix from `head`: every
-// gate inside S that reaches the head of all its qubits. Only the queues of
-// S's qubits matter (the diagonal gates a cluster carries afterwards never add
-// matrix gates), so this count ranks the candidate sets cheaply.
-int closure_size(const Dag& d, const std::vector<int>& head, uint64_t S) {
-    const auto& G = *d.g;
+// Gates the closure of qubit set S takes into its matrix from `head`. Only the
+// queues of S's qubits matter (the diagonal gates a cluster carries afterwards
+// never add matrix gates), so this count ranks the candidate sets cheaply.
+int closure_size(const Dag& d, const int* head, uint64_t S) {
     int h[64];
     for (uint64_t m = S; m; m &= m - 1) h[__builtin_ctzll(m)] = head[__builtin_ctzll(m)];
-    // taking a gate never makes another one unready, so the closure is the
-    // same in any order: a worklist of qubits whose queue head moved
     int cnt = 0;
-    for (uint64_t pending = S; pending;) {
-        const int q = __builtin_ctzll(pending);
-        pending &= pending - 1;
-        const auto& qq = d.queue[q];
-        while (h[q] < (int)qq.size()) {
-            const int gi = qq[h[q]];
-            const uint64_t gm = d.mask[gi];
-            if (gm & ~S) break;
-            bool at_head = true;
-            for (int j = 0; j < G[gi].nq && at_head; ++j) {
-                const int p = G[gi].q[j];
-                at_head = h[p] < (int)d.queue[p].size() && d.queue[p][h[p]] == gi;
-            }
-            if (!at_head) break;
-            for (int j = 0; j < G[gi].nq; ++j) h[G[gi].q[j]]++;
-            ++cnt;
-            pending |= gm & ~(uint64_t(1) << q);
-        }
-    }
+    d.closure(h, S, [&](const Dag::Item& x) { return !(x.mask & ~S); }, [&](const Dag::Item&) { ++cnt; });
     return cnt;
 }
 
@@ -414,55 +461,43 @@ double grown_cost(const OpCostFn& cost, const Grown& c, int n) {
 // best of the distinct candidates (by gates taken, ties in the order the
 // greedy choice breaks them; rank 0 is the greedy choice) instead of the
 // best; an empty schedule when there are not that many.
-std::vector<SOp> greedy_ops(int n, const std::vector<SGate>& gates, const std::vector<char>& dropped, int n_applied,
-                            int kcap_in, bool fuse_diag, const OpCostFn* trim = nullptr,
+std::vector<SOp> greedy_ops(const Dag& d, const std::vector<SGate>& gates, int n_applied, int kcap_in,
+                            bool fuse_diag, const OpCostFn* trim = nullptr,
                             const std::vector<uint64_t>* sets = nullptr, int first_cap = 0, int dev_step = -1,
                             int dev_rank = 0) {
-    const int ng = (int)gates.size();
+    const int n = d.n;
     std::vector<SOp> out;
-    Dag d;
-    d.n = n;
-    d.g = &gates;
-    d.queue.assign(n, {});
-    d.mask.assign(ng, 0);
-    for (int i = 0; i < ng; ++i) {
-        for (int j = 0; j < gates[i].nq; ++j) d.mask[i] |= uint64_t(1) << gates[i].q[j];
-        if (dropped[i]) continue;
-        for (int j = 0; j < gates[i].nq; ++j) d.queue[gates[i].q[j]].push_back(i);
-    }
-    std::vector<int> head(n, 0);
+    int head[64], head_before[64];
+    std::copy(d.first, d.first + n, head);
     int remaining = n_applied;
-    std::vector<int> rl;
+    std::vector<const Dag::Item*> rl;
     const int kmax = kcap_in;
     // closure sizes of the candidate sets, recomputed only for sets with a
     // qubit whose queue head moved since (the size depends on those heads only)
     std::vector<int> csize(sets ? sets->size() : 0, 0);
     uint64_t moved = ~uint64_t(0);
-    std::vector<int> head_before;
     int n_clusters = 0;
 
     while (remaining > 0) {
         d.ready_list(head, rl);
-        Frontier f0;
-        for (int q = 0; q < n; ++q) f0.head[q] = head[q];
-        f0.nrl = (int)rl.size();
-        std::copy(rl.begin(), rl.end(), f0.rl);
         const int kcur = (first_cap > 0 && n_clusters < 2) ? std::min(kmax, first_cap) : kmax;
-        int best_score = -1, best_seed = -1, best_cap = kcur;
+        int best_score = -1, best_cap = kcur;
+        const Dag::Item* best_seed = nullptr;
         uint64_t best_within = 0;
         // the deviating step lists every candidate: (score, seed, cap, within, qubits)
         const bool dev = (int)out.size() == dev_step;
         struct DevCand {
-            int score, seed, cap;
+            int score, cap;
+            const Dag::Item* seed;
             uint64_t within, Q;
         };
         std::vector<DevCand> devc;
-        for (int seed : rl) {
+        for (const Dag::Item* seed : rl) {
             // a gate wider than the cap (a dense gate) forms a cluster of its own width
-            const int khi = std::max(kcur, popc(d.mask[seed]));
-            Grown g;
-            const int c = grow(d, f0, seed, khi, fuse_diag, 0, dev ? &g : nullptr);
-            if (dev) devc.push_back({c, seed, khi, 0, g.Q});
+            const int khi = std::max(kcur, (int)seed->nq);
+            uint64_t Q = 0;
+            const int c = grow(d, head, rl, seed, khi, fuse_diag, 0, &Q, nullptr);
+            if (dev) devc.push_back({c, khi, seed, 0, Q});
             if (c > best_score) {
                 best_score = c;
                 best_seed = seed;
@@ -485,12 +520,12 @@ std::vector<SOp> greedy_ops(int n, const std::vector<SGate>& gates, const std::v
             std::partial_sort(ranked.begin(), ranked.begin() + top, ranked.end());
             for (size_t i = 0; i < top; ++i) {
                 if (popc(ranked[i].second) > kcur) continue;
-                Grown g;
-                const int c = grow(d, f0, -1, kcur, fuse_diag, ranked[i].second, dev ? &g : nullptr);
-                if (dev && c > 0) devc.push_back({c, -1, kcur, ranked[i].second, g.Q});
+                uint64_t Q = 0;
+                const int c = grow(d, head, rl, nullptr, kcur, fuse_diag, ranked[i].second, &Q, nullptr);
+                if (dev && c > 0) devc.push_back({c, kcur, nullptr, ranked[i].second, Q});
                 if (c > best_score) {  // c > 0: the closure took a matrix gate
                     best_score = c;
-                    best_seed = -1;
+                    best_seed = nullptr;
                     best_cap = kcur;
                     best_within = ranked[i].second;
                 }
@@ -513,17 +548,17 @@ std::vector<SOp> greedy_ops(int n, const std::vector<SGate>& gates, const std::v
             best_within = ch.within;
         }
         Grown best;
-        grow(d, f0, best_seed, best_cap, fuse_diag, best_within, &best);
-        if (trim && best_seed >= 0 && kcur > 1 && popc(best.Q) == kcur && popc(d.mask[best_seed]) < kcur) {
+        grow(d, head, rl, best_seed, best_cap, fuse_diag, best_within, nullptr, &best);
+        if (trim && best_seed && kcur > 1 && popc(best.Q) == kcur && best_seed->nq < kcur) {
             Grown small;
-            grow(d, f0, best_seed, kcur - 1, fuse_diag, 0, &small);
+            grow(d, head, rl, best_seed, kcur - 1, fuse_diag, 0, nullptr, &small);
             if (!all_diag(gates, small) && !all_diag(gates, best)) {
                 const double per_big = grown_cost(*trim, best, n) / best.n_gates();
                 const double per_small = grown_cost(*trim, small, n) / small.n_gates();
                 if (per_small < per_big) best = std::move(small);
             }
         }
-        head_before = head;
+        std::copy(head, head + n, head_before);
         SOp op;
         if (all_diag(gates, best)) {
             // a diagonal pass: take every ready diagonal gate, repeatedly
@@ -532,13 +567,12 @@ std::vector<SOp> greedy_ops(int n, const std::vector<SGate>& gates, const std::v
             for (;;) {
                 d.ready_list(head, rl);
                 bool took = false;
-                for (int gi : rl) {
-                    if (!gates[gi].diag) continue;
-                    const bool cz = gates[gi].kind == G_CZ;
-                    if ((cz && ncz >= kEpiMax) || (!cz && nph >= kEpiMax)) continue;
-                    (cz ? ncz : nph)++;
-                    op.members.push_back(gi);
-                    d.pop(head, gi);
+                for (const Dag::Item* x : rl) {
+                    if (!x->diag) continue;
+                    if ((x->cz ? ncz : nph) >= kEpiMax) continue;
+                    (x->cz ? ncz : nph)++;
+                    op.members.push_back(x->gi);
+                    d.pop(head, *x, __builtin_ctzll(x->mask));
                     took = true;
                 }
                 if (!took) break;
@@ -553,7 +587,7 @@ std::vector<SOp> greedy_ops(int n, const std::vector<SGate>& gates, const std::v
             op.epi = best.epi;
             std::sort(op.members.begin(), op.members.end());
             std::sort(op.epi.begin(), op.epi.end());
-            head = best.head;
+            std::copy(best.head, best.head + n, head);
             remaining -= best.n_gates();
             ++n_clusters;
         }
@@ -725,6 +759,7 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
     }
 
     const int kmax = std::max(1, std::min(o.kmax, kMaxK));
+    const Dag dag(n, gates, S.dropped);
     // candidate qubit sets (dense sets of the interaction graph, two slacks)
     std::vector<uint64_t> sets0, sets1;
     if (o.cluster_sets && kmax >= 2) dense_sets(n, gates, S.dropped, kmax, sets0, sets1);
@@ -745,14 +780,14 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
         for (int fc = 0; fc < first_caps; ++fc) {
             const int cap = fc ? 6 : 0;
             fns.push_back([&, cap]() {
-                return greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr, nullptr, cap);
+                return greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr, nullptr, cap);
             });
             if (sets0.empty()) continue;
             fns.push_back([&, cap]() {
-                return greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr, &sets0, cap);
+                return greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr, &sets0, cap);
             });
             fns.push_back([&, cap]() {
-                return greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr, &sets1, cap);
+                return greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr, &sets1, cap);
             });
         }
         const size_t ndev0 = fns.size();
@@ -760,12 +795,13 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
             for (int st = 0; st < kDevSteps; ++st)
                 for (int r = 1; r <= kDevRanks; ++r)
                     fns.push_back([&, st, r]() {
-                        return greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr, dev_sets, 0,
+                        return greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr, dev_sets, 0,
                                           st, r);
                     });
         std::vector<int> key(fns.size(), 0);  // start the deviations and the set-based schedules first
         for (size_t i = 0; i < fns.size(); ++i) key[i] = i >= ndev0 ? 2 : (i % 3 ? 1 : 0);
-        std::vector<std::vector<SOp>> res = run_tasks(o.parallel, fns, nullptr, &key);
+        const bool pool = o.parallel && fns.size() * (size_t)S.n_applied >= kPoolGates;
+        std::vector<std::vector<SOp>> res = run_tasks(pool, fns, nullptr, &key);
         double best = 0.0;
         for (size_t c = 0; c < res.size(); ++c) {
             std::vector<SOp>& ops = res[c];
@@ -846,17 +882,17 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
         key.push_back(k);
     };
     for (int kc = k_lo; kc <= kmax; ++kc)  // the plain schedules first: their prices decide which caps qualify
-        add(0, [&, kc]() { return priced(greedy_ops(n, gates, S.dropped, S.n_applied, kc, o.fuse_diag)); });
+        add(0, [&, kc]() { return priced(greedy_ops(dag, gates, S.n_applied, kc, o.fuse_diag)); });
     if (first_caps > 1) {  // the widest cap after a 6-qubit start, with and without the candidate sets
         add(0, [&]() {
-            return priced(greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr, nullptr, 6));
+            return priced(greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr, nullptr, 6));
         });
         for (const std::vector<uint64_t>* fs : {&sets0, &sets1})
             if (!fs->empty())
                 add(
                     0,
                     [&, fs]() {
-                        return priced(greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr, fs, 6));
+                        return priced(greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr, fs, 6));
                     },
                     1);
     }
@@ -869,7 +905,7 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
                 add(
                     -1,
                     [&, st, r]() {
-                        std::vector<SOp> ops = greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr,
+                        std::vector<SOp> ops = greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr,
                                                           dev_sets, 0, st, r);
                         if (ops.empty()) return Cand(std::vector<SOp>(), -1.0);  // no candidate of that rank
                         return priced(std::move(ops));
@@ -877,7 +913,7 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
                     2);
     if (kmax > 1)
         add(kmax - 1,
-            [&]() { return priced(greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, &cost)); });
+            [&]() { return priced(greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, &cost)); });
     // set families: kmax's are at hand; a narrower cap's are found inside
     // its tasks, one task per (cap, slack)
     if (o.cluster_sets)
@@ -890,7 +926,7 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
                         0,
                         [&, fs]() {
                             return priced(
-                                greedy_ops(n, gates, S.dropped, S.n_applied, kmax, o.fuse_diag, nullptr, fs));
+                                greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, nullptr, fs));
                         },
                         1);
                 } else {
@@ -899,7 +935,7 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
                         dense_sets(n, gates, S.dropped, kc, a, b);
                         const std::vector<uint64_t>& sets = slack ? b : a;
                         if (sets.empty()) return Cand(std::vector<SOp>(), -1.0);  // no such family: not a candidate
-                        return priced(greedy_ops(n, gates, S.dropped, S.n_applied, kc, o.fuse_diag, nullptr, &sets));
+                        return priced(greedy_ops(dag, gates, S.n_applied, kc, o.fuse_diag, nullptr, &sets));
                     });
                 }
             }

@@ -70,9 +70,10 @@ constexpr int kFoldTableBits6 = 7;
 constexpr int kFoldTableBits7 = 6;
 // The one-deviation search (schedules that take, at one of the first
 // kDevSteps steps, one of the kDevRanks next-best clusters instead of the
-// best, a limited-discrepancy search) costs about 0.7 ms of host time; it
-// runs where a pass takes longer than that (states of at least
-// kDevMinQubits qubits) and candidates are built in parallel.
+// best, a limited-discrepancy search) takes most of the host time of a schedule
+// (0.57 ms in all for the 30-qubit depth-25 circuit); it runs where a pass
+// takes longer than that (states of at least kDevMinQubits qubits) and
+// candidates are built in parallel.
 constexpr int kDevSteps = 3;
 constexpr int kDevRanks = 4;
 constexpr int kDevMinQubits = 29;
