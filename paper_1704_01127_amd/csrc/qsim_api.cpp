@@ -13,6 +13,7 @@
 
 #include "api_common.h"
 #include "qsim_internal.h"
+#include "staging.h"
 #include "scheduler.h"
 
 using namespace qsim;
@@ -301,27 +302,55 @@ qsim_status flush(qsim_state_s* s, Chunk& c) {
     const size_t eb = db + align256(c.dense.size() * sizeof(double));
     const size_t total = eb + align256(c.epis.size() * sizeof(EpiDesc));
     if (total > kDescBytes) return fail(QSIM_E_UNSUPPORTED, "descriptor chunk too large");
-    std::vector<char> host(total, 0);
-    if (!c.bops.empty()) std::memcpy(host.data() + ob, c.bops.data(), c.bops.size() * sizeof(BuildOp));
-    if (!c.bgates.empty()) std::memcpy(host.data() + gb, c.bgates.data(), c.bgates.size() * sizeof(BuildGate));
-    if (!c.dense.empty()) std::memcpy(host.data() + db, c.dense.data(), c.dense.size() * sizeof(double));
-    if (!c.epis.empty()) std::memcpy(host.data() + eb, c.epis.data(), c.epis.size() * sizeof(EpiDesc));
     char* dev = s->ws + kDescOff;
     char* mats = s->ws + kMatOff;
-    if (total) HIP_TRY(hipMemcpyAsync(dev, host.data(), total, hipMemcpyHostToDevice, s->st), "upload descriptors");
-    if (!c.bops.empty()) {
+    int kmax = 1;
+    for (const BuildOp& bo : c.bops) kmax = std::max(kmax, (int)bo.k);
+    // The builder reads small descriptors from a pinned block itself and puts
+    // the epilogues, which every cluster launch reads, into the workspace. A
+    // dense gate behind others is read more than once: those go by a copy.
+    bool direct = total > 0 && total <= kStageBytes && (int)c.bops.size() < kStageFlags / build_parts(kMaxK);
+    for (const BuildOp& bo : c.bops)
+        for (int i = 0; direct && bo.n_gates > 1 && i < bo.n_gates; ++i)
+            direct = c.bgates[bo.gate0 + i].kind != G_DENSE;
+    StageBlock* block = direct ? stage_acquire(s->st) : nullptr;
+    std::vector<char> pageable;
+    if (!block) pageable.resize(total);
+    char* host = block ? block->host : pageable.data();
+    if (!c.bops.empty()) std::memcpy(host + ob, c.bops.data(), c.bops.size() * sizeof(BuildOp));
+    if (!c.bgates.empty()) std::memcpy(host + gb, c.bgates.data(), c.bgates.size() * sizeof(BuildGate));
+    if (!c.dense.empty()) std::memcpy(host + db, c.dense.data(), c.dense.size() * sizeof(double));
+    if (!c.epis.empty()) std::memcpy(host + eb, c.epis.data(), c.epis.size() * sizeof(EpiDesc));
+    const char* src = block ? block->dev : dev;
+    if (!block && total)
+        HIP_TRY(hipMemcpyAsync(dev, host, total, hipMemcpyHostToDevice, s->st), "upload descriptors");
+    BuildTail tail;
+    if (block) {
+        tail.src = block->dev + eb;
+        tail.dst = dev + eb;
+        tail.bytes = total - eb;
+        tail.flags = block->dev_flags();
+        tail.seq = block->seq;
+        if (c.bops.size() == 1 && c.bops[0].n_gates == 1) {
+            tail.one = 1;
+            tail.op = c.bops[0];
+            tail.gate = c.bgates[c.bops[0].gate0];
+        }
+    }
+    if (!c.bops.empty() || block) {
         OpRecord r;
         std::memset(&r, 0, sizeof(r));
         r.kind = 5;
         r.k = (int)c.bops.size();
-        int kmax = 1;
-        for (const BuildOp& bo : c.bops) kmax = std::max(kmax, (int)bo.k);
-        HIP_TRY(rec_begin(s, r), "event record");
-        HIP_TRY(launch_build(reinterpret_cast<const BuildOp*>(dev + ob), (int)c.bops.size(), kmax,
-                             reinterpret_cast<const BuildGate*>(dev + gb),
-                             reinterpret_cast<const double*>(dev + db), mats, s->st),
+        if (r.k) HIP_TRY(rec_begin(s, r), "event record");
+        int groups = 0;
+        // a block whose launch failed is not used again
+        HIP_TRY(launch_build(reinterpret_cast<const BuildOp*>(src + ob), (int)c.bops.size(), kmax,
+                             reinterpret_cast<const BuildGate*>(src + gb),
+                             reinterpret_cast<const double*>(src + db), mats, tail, &groups, s->st),
                 "matrix build launch");
-        HIP_TRY(rec_end(s, r), "event record");
+        if (block) stage_release(block, groups);
+        if (r.k) HIP_TRY(rec_end(s, r), "event record");
     }
     const EpiDesc* epis = reinterpret_cast<const EpiDesc*>(dev + eb);
     const size_t sb = slot_bytes(s->dbl, s->kmax_ws);
@@ -706,6 +735,28 @@ qsim_status add_gate(qsim_state_s* s, Chunk& c, const qsim_gate* gates, int gi) 
     c.items.push_back(it);
     return QSIM_OK;
 }
+
+// The eight sums of a reduction: written by its last launch to a pinned block
+// (or to the workspace, and copied), valid after fetch().
+struct Sums {
+    qsim_state_s* s;
+    StageBlock* block;
+    double* dev;
+    double v[8] = {};
+    explicit Sums(qsim_state_s* s_)
+        : s(s_), block(stage_acquire(s_->st)), dev(reinterpret_cast<double*>(block ? block->dev : s_->ws + kResOff)) {}
+    hipError_t fetch() {
+        hipError_t e = hipSuccess;
+        if (!block) e = hipMemcpyAsync(v, dev, sizeof(v), hipMemcpyDeviceToHost, s->st);
+        if (e == hipSuccess) e = hipStreamSynchronize(s->st);
+        if (e == hipSuccess && block) {  // else the block may still be written: it is not used again
+            std::memcpy(v, block->host, sizeof(v));
+            stage_release(block, 0);
+        }
+        return e;
+    }
+    double operator[](int i) const { return v[i]; }
+};
 
 qsim_status check_state(qsim_state s) {
     if (!s) return fail(QSIM_E_INVALID, "null state handle");
@@ -1112,16 +1163,14 @@ qsim_status qsim_probs(qsim_state s, void* dev_out, qsim_dtype out_dt, double* n
     if (qsim_status r = check_state(s)) return r;
     if (dev_out && out_dt != QSIM_C64 && out_dt != QSIM_C128) return fail(QSIM_E_INVALID, "unknown out dtype");
     double* part = reinterpret_cast<double*>(s->ws);
-    double* res = reinterpret_cast<double*>(s->ws + kResOff);
+    Sums h(s);
     if (!dev_out && s->stats_ready) {  // the sums of the last run's final pass
-        HIP_TRY(launch_reduce_stats(part, s->stats_blocks, res, s->st), "stats reduce launch");
+        HIP_TRY(launch_reduce_stats(part, s->stats_blocks, h.dev, s->st), "stats reduce launch");
     } else {
         s->stats_ready = false;  // the partial area is rewritten
-        HIP_TRY(launch_stats(s->psi, s->dbl, s->n, dev_out, out_dt == QSIM_C128, part, res, s->st), "stats launch");
+        HIP_TRY(launch_stats(s->psi, s->dbl, s->n, dev_out, out_dt == QSIM_C128, part, h.dev, s->st), "stats launch");
     }
-    double h[8];
-    HIP_TRY(hipMemcpyAsync(h, res, 8 * sizeof(double), hipMemcpyDeviceToHost, s->st), "stats copy");
-    HIP_TRY(hipStreamSynchronize(s->st), "stats sync");
+    HIP_TRY(h.fetch(), "stats sync");
     if (norm) *norm = h[0];
     if (sum_p2) *sum_p2 = h[1];
     if (entropy_nats) *entropy_nats = h[2];
@@ -1134,12 +1183,10 @@ qsim_status qsim_compare(qsim_state s, const void* dev_ref, qsim_dtype ref_dt, d
     if (!dev_ref) return fail(QSIM_E_INVALID, "null reference");
     if (ref_dt != QSIM_C64 && ref_dt != QSIM_C128) return fail(QSIM_E_INVALID, "unknown reference dtype");
     double* part = reinterpret_cast<double*>(s->ws);
-    double* res = reinterpret_cast<double*>(s->ws + kResOff);
+    Sums h(s);
     s->stats_ready = false;  // the partial area is rewritten
-    HIP_TRY(launch_compare(s->psi, s->dbl, s->n, dev_ref, ref_dt == QSIM_C128, part, res, s->st), "compare launch");
-    double h[8];
-    HIP_TRY(hipMemcpyAsync(h, res, 8 * sizeof(double), hipMemcpyDeviceToHost, s->st), "compare copy");
-    HIP_TRY(hipStreamSynchronize(s->st), "compare sync");
+    HIP_TRY(launch_compare(s->psi, s->dbl, s->n, dev_ref, ref_dt == QSIM_C128, part, h.dev, s->st), "compare launch");
+    HIP_TRY(h.fetch(), "compare sync");
     const double dot2 = h[0] * h[0] + h[1] * h[1];
     if (fidelity) *fidelity = (h[2] > 0 && h[3] > 0) ? dot2 / (h[2] * h[3]) : 0.0;
     if (max_abs_diff) *max_abs_diff = h[4];

@@ -485,9 +485,10 @@ qsim_status qsim_batch_run(qsim_batch b, void* dev_workspace, size_t ws_bytes, v
     HIP_TRY(hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, st), "upload batch descriptors");
     int build_kmax = 1;
     for (const BuildOp& bo : b->bops) build_kmax = std::max(build_kmax, (int)bo.k);
+    int groups = 0;
     HIP_TRY(launch_build(reinterpret_cast<const BuildOp*>(ws + b->off_bops), (int)b->bops.size(), build_kmax,
                          reinterpret_cast<const BuildGate*>(ws + b->off_bgates),
-                         reinterpret_cast<const double*>(ws + b->off_dense), ws + b->off_mats, st),
+                         reinterpret_cast<const double*>(ws + b->off_dense), ws + b->off_mats, BuildTail(), &groups, st),
             "matrix build launch");
 
     int dev = 0, cus = 0, clock_khz = 0;

@@ -231,9 +231,26 @@ hipError_t launch_fold2(void* psi, const ClusterGeom& g2, const void* mat2, cons
 // and its diagonal epilogue, written in one pass.
 hipError_t launch_init_cluster(void* psi, bool dbl, const ClusterGeom& g, const void* mat, const EpiDesc* epi,
                                hipStream_t st);
-// Builds n_ops matrices of at most kmax qubits (device descriptors).
+// Work-groups of the builder per matrix of k qubits.
+__host__ __device__ constexpr int build_parts(int k) { return k <= 5 ? 1 : (k == 6 ? 4 : 8); }
+// A builder launch whose descriptors lie in pinned host memory also copies
+// `bytes` (a multiple of 16) from src to dst, and stores seq in a flag per
+// work-group as it ends (flags null: neither). The op and the gate of a launch
+// with one of each (`one`) come with its arguments: two trips over the link less.
+struct BuildTail {
+    int32_t one = 0;
+    BuildOp op{};
+    BuildGate gate{};
+    const char* src = nullptr;
+    char* dst = nullptr;
+    size_t bytes = 0;
+    uint32_t* flags = nullptr;
+    uint32_t seq = 0;
+};
+// Builds n_ops matrices of at most kmax qubits; *groups receives the number of
+// work-groups (flags of the tail).
 hipError_t launch_build(const BuildOp* ops, int n_ops, int kmax, const BuildGate* gates, const double* dense,
-                        char* mat_base, hipStream_t st);
+                        char* mat_base, const BuildTail& tail, int* groups, hipStream_t st);
 // Variant of the cluster kernel chosen for (dtype, k, n, targets).
 int cluster_layout(bool dbl, int k, int n);
 // variant (matrix-core layouts, k <= 5): 0 = direct register gather, 1 = LDS-staged.

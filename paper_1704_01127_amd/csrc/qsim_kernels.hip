@@ -3635,9 +3635,8 @@ constexpr int kBuildThreads = 256;
 constexpr int kBuildCols = 4;        // columns per lane
 constexpr int kBuildGateChunk = 64;  // gates staged in LDS at a time
 
-// Work-groups per matrix of k qubits (kBuildThreads / 64 waves of
-// kBuildCols * 2^(6-k) columns each; kBuildCols for k = 7).
-__host__ __device__ constexpr int build_parts(int k) { return k <= 5 ? 1 : (k == 6 ? 4 : 8); }
+// build_parts(k) work-groups per matrix of k qubits hold kBuildThreads / 64
+// waves of kBuildCols * 2^(6-k) columns each; kBuildCols for k = 7.
 
 struct BuildLds {
     // gates of the current chunk; op: 0 CZ, 1 diagonal one-qubit (phase m[6..7]
@@ -3651,7 +3650,8 @@ struct BuildLds {
 // R registers per column: 2 for k = 7 (row bit 6), else 1.
 template <int R>
 __device__ __forceinline__ void build_matrix(const BuildOp& op, int part, const BuildGate* __restrict__ gates,
-                                             const double* __restrict__ dense, char* __restrict__ out, BuildLds& L) {
+                                             const BuildTail& tail, const double* __restrict__ dense,
+                                             char* __restrict__ out, BuildLds& L) {
     constexpr int C = kBuildCols;
     const int k = R == 2 ? 7 : op.k, D = 1 << k;
     const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
@@ -3672,7 +3672,8 @@ __device__ __forceinline__ void build_matrix(const BuildOp& op, int part, const 
         if (g0) __syncthreads();  // the previous chunk has been read
         if ((int)threadIdx.x < ng) {
             const int t = (int)threadIdx.x;
-            const BuildGate bg = gates[op.gate0 + g0 + t];
+            BuildGate bg = tail.gate;
+            if (!tail.one) bg = gates[op.gate0 + g0 + t];
             L.op[t] = bg.kind == G_CZ ? 0 : (bg.kind == G_DENSE ? 3 : (gate_is_diagonal(bg.kind) ? 1 : 2));
             L.nq[t] = bg.nq;
             L.off[t] = bg.dense_off;
@@ -3954,18 +3955,46 @@ __device__ __forceinline__ void build_matrix(const BuildOp& op, int part, const 
     }
 }
 
-__global__ __launch_bounds__(kBuildThreads) void k_build(const BuildOp* __restrict__ ops,
+// With a tail (see BuildTail), ops, gates and dense lie in pinned host memory:
+// a work-group reads its gates into LDS in one round and a dense gate's
+// entries once each, so they come over the link as fast as a copy would bring
+// them, without the copy's launch and the host's wait for it. The launch itself
+// takes longer (11 matrices of a 20-qubit circuit 17.8 us instead of 16.3, one
+// dense 3-qubit gate 4.5 instead of 3.9); the 20-qubit depth-25 circuit went
+// from 343 to 293 us with its sums also written to pinned memory, the 12-qubit
+// one of depth 16 from 124 to 87. The work-groups
+// behind the last matrix copy the tail; each one stores its flag when its
+// reads have been consumed.
+__global__ __launch_bounds__(kBuildThreads) void k_build(const BuildOp* __restrict__ ops, int n_ops,
                                                          const BuildGate* __restrict__ gates,
-                                                         const double* __restrict__ dense, char* __restrict__ mat_base) {
+                                                         const double* __restrict__ dense, char* __restrict__ mat_base,
+                                                         BuildTail tail) {
     __shared__ BuildLds L;
-    const BuildOp op = ops[blockIdx.x];
     const int part = (int)blockIdx.y;
-    if (part >= build_parts(op.k)) return;  // the grid is sized for the widest matrix
-    char* out = mat_base + op.out_off;
-    if (op.k == 7)
-        build_matrix<2>(op, part, gates, dense, out, L);
-    else
-        build_matrix<1>(op, part, gates, dense, out, L);
+    if ((int)blockIdx.x < n_ops) {
+        BuildOp op = tail.op;
+        if (!tail.one) op = ops[blockIdx.x];
+        char* out = mat_base + op.out_off;
+        if (part < build_parts(op.k)) {  // the grid is sized for the widest matrix
+            if (op.k == 7)
+                build_matrix<2>(op, part, gates, tail, dense, out, L);
+            else
+                build_matrix<1>(op, part, gates, tail, dense, out, L);
+        }
+    } else {
+        const uint4* src = reinterpret_cast<const uint4*>(tail.src);
+        uint4* dst = reinterpret_cast<uint4*>(tail.dst);
+        for (size_t i = (size_t)part * kBuildThreads + threadIdx.x; i < tail.bytes / 16;
+             i += (size_t)gridDim.y * kBuildThreads)
+            dst[i] = src[i];
+    }
+    if (tail.flags) {
+        __builtin_amdgcn_s_waitcnt(0);  // this wave's reads, also those nothing used
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(tail.flags + blockIdx.y * gridDim.x + blockIdx.x, tail.seq, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // ------------------------------------------------------------ float64 reductions
@@ -4288,10 +4317,11 @@ hipError_t launch_init_cluster(void* psi, bool dbl, const ClusterGeom& g, const 
 }
 
 hipError_t launch_build(const BuildOp* ops, int n_ops, int kmax, const BuildGate* gates, const double* dense,
-                        char* mat_base, hipStream_t st) {
-    if (n_ops <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_build, dim3(n_ops, build_parts(kmax)), dim3(kBuildThreads), 0, st, ops, gates, dense,
-                       mat_base);
+                        char* mat_base, const BuildTail& tail, int* groups, hipStream_t st) {
+    const int nx = n_ops + (tail.bytes > 0), ny = build_parts(kmax);
+    *groups = nx * ny;
+    if (nx <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_build, dim3(nx, ny), dim3(kBuildThreads), 0, st, ops, n_ops, gates, dense, mat_base, tail);
     return hipGetLastError();
 }
 
@@ -4699,9 +4729,20 @@ unsigned launch_stream(uint64_t units, bool nt, F&& go) {
 }
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
+// Up to this many units one work-group takes the sums of a state alone, with
+// no second launch (two rounds of 8 accesses a lane).
+constexpr uint64_t kAloneUnits = 4096;
+
 template <typename T, typename P, int W>
 void launch_stats_t(const void* psi, int n, void* probs, double* part, double* res, hipStream_t st) {
     const uint64_t units = (uint64_t(1) << n) / W;
+    if (units <= kAloneUnits) {
+        if (units >= 8 * 256)
+            hipLaunchKernelGGL((k_stats<T, P, W, 8, false>), dim3(1), dim3(256), 0, st, psi, units, probs, res);
+        else
+            hipLaunchKernelGGL((k_stats<T, P, W, 1, false>), dim3(1), dim3(256), 0, st, psi, units, probs, res);
+        return;
+    }
     const unsigned grid = launch_stream(units, beyond_caches(n, sizeof(T) == 8), [&](unsigned g, auto u, auto nt) {
         hipLaunchKernelGGL((k_stats<T, P, W, decltype(u)::value, decltype(nt)::value>), dim3(g), dim3(256), 0, st, psi,
                            units, probs, part);
@@ -4712,6 +4753,13 @@ void launch_stats_t(const void* psi, int n, void* probs, double* part, double* r
 template <typename T, typename R, int W>
 void launch_compare_t(const void* psi, int n, const void* ref, double* part, double* res, hipStream_t st) {
     const uint64_t units = (uint64_t(1) << n) / W;
+    if (units <= kAloneUnits) {
+        if (units >= 8 * 256)
+            hipLaunchKernelGGL((k_compare<T, R, W, 8, false>), dim3(1), dim3(256), 0, st, psi, ref, units, res);
+        else
+            hipLaunchKernelGGL((k_compare<T, R, W, 1, false>), dim3(1), dim3(256), 0, st, psi, ref, units, res);
+        return;
+    }
     const unsigned grid = launch_stream(units, beyond_caches(n, sizeof(T) == 8), [&](unsigned g, auto u, auto nt) {
         hipLaunchKernelGGL((k_compare<T, R, W, decltype(u)::value, decltype(nt)::value>), dim3(g), dim3(256), 0, st,
                            psi, ref, units, part);
