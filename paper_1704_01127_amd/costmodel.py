@@ -99,9 +99,10 @@ def init_params(rng, n_in=N_IN, h=N_HIDDEN):
                            np.zeros(1)]).astype(np.float32)
 
 
-def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print):
+def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print, lr_end=0.1):
     """Train on the GPU with the library's kernels. x: [N, in] normalised
-    float32, y: [N] normalised. Returns (params, history)."""
+    float32, y: [N] normalised. The rate falls along a half cosine from lr to
+    lr * lr_end. Returns (params, history)."""
     import torch
     dev = torch.device("cuda")
     rng = np.random.default_rng(seed)
@@ -117,7 +118,7 @@ def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print):
         xb = xt.index_select(0, idx).contiguous()
         yb = yt.index_select(0, idx).contiguous()
         grad, loss = qsim.mlp_backward(p, N_IN, N_HIDDEN, xb, yb)
-        cur_lr = lr * (0.5 * (1 + math.cos(math.pi * step / steps)) * 0.9 + 0.1)
+        cur_lr = lr * (0.5 * (1 + math.cos(math.pi * step / steps)) * (1 - lr_end) + lr_end)
         qsim.mlp_adam(p, grad, m, v, step, cur_lr)
         if step % max(1, steps // 10) == 0 or step == 1:
             rec = {"step": step, "train_mse": float(loss.item())}
@@ -139,7 +140,8 @@ def cmd_train(args):
     y_mean, y_std = float(y[~held].mean()), float(y[~held].std())
     xn = ((x - mean) / std).astype(np.float32)
     yn = ((y - y_mean) / y_std).astype(np.float32)
-    params, hist = train(xn[~held], yn[~held], steps=args.steps, val=(xn[held], yn[held]))
+    params, hist = train(xn[~held], yn[~held], steps=args.steps, batch=args.batch, lr=args.lr,
+                         lr_end=args.lr_end, val=(xn[held], yn[held]))
     # validation error in log space -> typical relative error of a time prediction
     pred = qsim.mlp_predict_host(params, N_IN, N_HIDDEN, xn[held]) * y_std + y_mean
     rmse = float(np.sqrt(np.mean((pred - y[held]) ** 2)))
@@ -237,6 +239,9 @@ def main(argv=None):
     t = sub.add_parser("train")
     t.add_argument("--data", required=True)
     t.add_argument("--steps", type=int, default=4000)
+    t.add_argument("--batch", type=int, default=512)
+    t.add_argument("--lr", type=float, default=2e-3)
+    t.add_argument("--lr-end", type=float, default=0.1, help="last learning rate over the first")
     t.add_argument("--out", required=True)
     c = sub.add_parser("compare")
     c.add_argument("--n", default="28,29,30")

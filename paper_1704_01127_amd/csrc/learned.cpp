@@ -61,7 +61,7 @@ namespace {
 struct Model {
     bool loaded = false;
     int n_in = 0, n_hidden = 0;
-    std::vector<float> p;             // W1 [H][in], b1 [H], W2 [H][H], b2 [H], W3 [H], b3 [1]
+    std::vector<float> p;             // W1 [in][H], b1 [H], W2 [H][H] (input first), b2 [H], W3 [H], b3 [1]
     std::vector<float> mean, inv_std; // feature normalisation
     float y_mean = 0.f, y_std = 1.f;
 };
@@ -83,7 +83,10 @@ size_t mlp_param_count(int n_in, int h) { return (size_t)h * n_in + h + (size_t)
 // multiply-adds in index order). The loops run over the inputs outermost so
 // that the units' chains are independent of each other (and vectorise); every
 // chain keeps its order, so the result does not depend on the loop shape.
-template <bool kHwFma>
+// kInputFirst: W1 and W2 are stored with the input index first, as the loops
+// read them (the loaded model's; the public layout has the unit index first,
+// whose strided reads took most of a prediction's time).
+template <bool kHwFma, bool kInputFirst>
 static float mlp_forward_impl(const float* p, int n_in, int h, const float* x) {
     const float* W1 = p;
     const float* b1 = W1 + (size_t)h * n_in;
@@ -94,11 +97,13 @@ static float mlp_forward_impl(const float* p, int n_in, int h, const float* x) {
     float a1[256], a2[256];
     for (int i = 0; i < h; ++i) a1[i] = b1[i];
     for (int j = 0; j < n_in; ++j)
-        for (int i = 0; i < h; ++i) a1[i] = std::fma(W1[(size_t)i * n_in + j], x[j], a1[i]);
+        for (int i = 0; i < h; ++i) 
+            a1[i] = std::fma(kInputFirst ? W1[(size_t)j * h + i] : W1[(size_t)i * n_in + j], x[j], a1[i]);
     for (int i = 0; i < h; ++i) a1[i] = a1[i] > 0.f ? a1[i] : 0.f;
     for (int i = 0; i < h; ++i) a2[i] = b2[i];
     for (int j = 0; j < h; ++j)
-        for (int i = 0; i < h; ++i) a2[i] = std::fma(W2[(size_t)i * h + j], a1[j], a2[i]);
+        for (int i = 0; i < h; ++i) 
+            a2[i] = std::fma(kInputFirst ? W2[(size_t)j * h + i] : W2[(size_t)i * h + j], a1[j], a2[i]);
     for (int i = 0; i < h; ++i) a2[i] = a2[i] > 0.f ? a2[i] : 0.f;
     float y = b3[0];
     for (int j = 0; j < h; ++j) y = std::fma(W3[j], a2[j], y);
@@ -107,14 +112,18 @@ static float mlp_forward_impl(const float* p, int n_in, int h, const float* x) {
 
 // With the FMA instructions available, std::fma compiles to them instead of a
 // library call.
+template <bool kInputFirst>
 __attribute__((target("avx2,fma"))) static float mlp_forward_fma(const float* p, int n_in, int h, const float* x) {
-    return mlp_forward_impl<true>(p, n_in, h, x);
+    return mlp_forward_impl<true, kInputFirst>(p, n_in, h, x);
 }
 
-float mlp_forward_host(const float* p, int n_in, int h, const float* x) {
+template <bool kInputFirst>
+static float mlp_forward(const float* p, int n_in, int h, const float* x) {
     static const bool hw = __builtin_cpu_supports("avx2") && __builtin_cpu_supports("fma");
-    return hw ? mlp_forward_fma(p, n_in, h, x) : mlp_forward_impl<false>(p, n_in, h, x);
+    return hw ? mlp_forward_fma<kInputFirst>(p, n_in, h, x) : mlp_forward_impl<false, kInputFirst>(p, n_in, h, x);
 }
+
+float mlp_forward_host(const float* p, int n_in, int h, const float* x) { return mlp_forward<false>(p, n_in, h, x); }
 
 bool learned_model_loaded() { return current_model()->loaded; }
 
@@ -125,10 +134,14 @@ double learned_cost_us(int n, bool dbl, int k, const int* qubits, int n_epi, int
     if (!m->loaded) return 1.0;
     float x[kFeatures];
     for (int i = 0; i < kFeatures; ++i) x[i] = (f[i] - m->mean[i]) * m->inv_std[i];
-    const float y = mlp_forward_host(m->p.data(), m->n_in, m->n_hidden, x);
+    const float y = mlp_forward<true>(m->p.data(), m->n_in, m->n_hidden, x);
     const double log_us = (double)y * m->y_std + m->y_mean;
     return std::exp(log_us) * std::ldexp(1.0, n - 30);
 }
+
+// Predictions closer than the model's own error (4.4% on held-out ops) do not
+// tell two kernel variants apart.
+constexpr double kVariantMargin = 1.05;
 
 // Predicted time of an op with the faster of the two matrix-core kernel
 // variants (direct gather or LDS-staged tiles) where the op has both and no
@@ -140,7 +153,7 @@ double learned_cost_best_us(int n, bool dbl, int k, const int* qubits, int n_epi
         return learned_cost_us(n, dbl, k, qubits, n_epi, -1);
     const double t0 = learned_cost_us(n, dbl, k, qubits, n_epi, 0);
     const double t1 = learned_cost_us(n, dbl, k, qubits, n_epi, 1);
-    if (variant) *variant = t1 < t0 ? 1 : 0;
+    if (variant) *variant = t1 * kVariantMargin < t0 ? 1 : (t0 * kVariantMargin < t1 ? 0 : -1);
     return t1 < t0 ? t1 : t0;
 }
 
@@ -175,6 +188,12 @@ qsim_status qsim_set_cost_model(const float* params, int n_in, int n_hidden, con
     m.n_in = n_in;
     m.n_hidden = n_hidden;
     m.p.assign(params, params + mlp_param_count(n_in, n_hidden));
+    const float* w2 = params + (size_t)n_hidden * n_in + n_hidden;
+    float* v2 = m.p.data() + (w2 - params);
+    for (int i = 0; i < n_hidden; ++i) {
+        for (int j = 0; j < n_in; ++j) m.p[(size_t)j * n_hidden + i] = params[(size_t)i * n_in + j];
+        for (int j = 0; j < n_hidden; ++j) v2[(size_t)j * n_hidden + i] = w2[(size_t)i * n_hidden + j];
+    }
     m.mean.assign(feat_mean, feat_mean + n_in);
     m.inv_std.resize(n_in);
     for (int i = 0; i < n_in; ++i) m.inv_std[i] = feat_std[i] > 0 ? 1.0f / feat_std[i] : 0.0f;
