@@ -130,6 +130,16 @@ __device__ __forceinline__ uint32_t xcd_block() {
     return (g & 7) == 0 ? (b & 7) * (g >> 3) + (b >> 3) : b;
 }
 
+// Work-group number of a launch that covers a state with one work-group per
+// kWgBytes of it: in memory order beyond the caches (see beyond_caches), else
+// by stretches, one per XCD. Passes that follow each other then find what fits
+// in an XCD's L2 (4 MiB) where the last one left it: 363 gates one by one on a
+// 20-qubit complex128 state (16 MiB) 1.91 ms, in memory order 2.38.
+template <uint32_t kWgBytes>
+__device__ __forceinline__ uint32_t tile_block() {
+    return gridDim.x < (uint32_t(512) << 20) / kWgBytes ? xcd_block() : blockIdx.x;
+}
+
 // Float64 sums of p = |a|^2 (slot 0), p^2 (slot 1) and -p ln p (slot 2) over
 // float amplitudes. ln p = e ln 2 + ln m with p = m 2^e split exactly and
 // ln m (m in [1/2, 1)) in float, within ~1.4e-7 absolute - far below what a
@@ -658,7 +668,7 @@ __global__ __launch_bounds__(256, 2) void k_cluster_f32_split6(float2* __restric
     constexpr bool PAIR = !LOWT;
     const int cpair = PAIR ? 2 * (p & 15) : p;
     const uint64_t cown = PAIR ? (uint64_t)((p >> 4) & 1) : 0;
-    const uint64_t tile = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint64_t tile = (uint64_t)tile_block<4 * 2048 * 8>() * 4 + (threadIdx.x >> 6);
     const uint64_t base = deposit_cols<K>(tile * 32 + cpair, g);
     const uint64_t b0 = base | (h ? uint64_t(1) << g.t[K - 1] : 0) | (cown ? uint64_t(1) << g.t[0] : 0);
     float X[2 * HX];
@@ -1212,7 +1222,7 @@ __global__ __launch_bounds__(256, NB == 1 ? 4 : 2) void k_cluster_f64_mfma(vd2* 
     __shared__ double As[RB * S * 64];
     const int lane = threadIdx.x & 63, p = lane & 15, q = lane >> 4;
     const uint64_t qoff = ((q & 1) ? (uint64_t(1) << g.t[K - 2]) : 0) | ((q & 2) ? (uint64_t(1) << g.t[K - 1]) : 0);
-    const uint64_t tile = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint64_t tile = (uint64_t)tile_block<4 * D * COLS * 16>() * 4 + (threadIdx.x >> 6);
     const bool act = tile < g.ncols / COLS;
     uint64_t base[NB];
     double B[NB][2 * HX];
@@ -1625,7 +1635,7 @@ __global__ __launch_bounds__(256, C == 4 ? 4 : 2) void k_cluster_f64_stage(vd2* 
 #pragma unroll
     for (int b = 0; b < 6; ++b)
         if ((lane >> b) & 1) lane_off |= uint64_t(1) << sg.tb[b];
-    const uint64_t tile = (uint64_t)blockIdx.x * 4 + w;
+    const uint64_t tile = (uint64_t)tile_block<4 * (1 << TB) * 16>() * 4 + w;
     const bool act = tile < (g.ncols >> C);
     const uint64_t tb0 = tile_base<TB>(tile, sg);
     vd2 R[NL];
@@ -2350,7 +2360,7 @@ __global__ __launch_bounds__(256, 2) void k_cluster_f32_split6s(float2* __restri
     __shared__ half8 L[2 * NP];
     const int lane = threadIdx.x & 63, p = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t tile = (uint64_t)blockIdx.x * 4 + w;
+    const uint64_t tile = (uint64_t)tile_block<4 * 2048 * 8>() * 4 + w;
     const bool act = tile < ntiles;
     vf4* T4 = reinterpret_cast<vf4*>(L) + w * 1024;  // this wave's tile
     constexpr bool PAIR = !LOWT;
@@ -3382,32 +3392,39 @@ template <typename T>
 struct Gate2x2 {
     T m[8];
 };
+// Units of a thread: 8 in flight. In the caches (not NT) MODE 0 takes 4, for
+// more wavefronts: 23 / 24 qubits complex128, H on the highest qubit 38.4 /
+// 71.7 us against 41.1 / 73.5; on whole lines 8 are as fast or faster.
+constexpr int gate1q_units(int mode, bool nt) { return mode == 0 && !nt ? 4 : 8; }
+
 template <typename T, int MODE, bool NT>
 __global__ __launch_bounds__(256, 6) void k_gate1q(typename Unit<T>::type* __restrict__ psi, int ub, Gate2x2<T> g,
                                                 uint64_t units) {
     using V = typename Unit<T>::type;
     constexpr int A = Unit<T>::AMPS;
     const T* m = g.m;
+    constexpr int PER = gate1q_units(MODE, NT);
+    const uint32_t wg = tile_block<256 * PER * 16>();
     // row of the 2x2: c0 a + c1 b
     auto row = [](T c0r, T c0i, T c1r, T c1i, T ar, T ai, T br, T bi, T& re, T& im) {
         re = (c0r * ar - c0i * ai) + (c1r * br - c1i * bi);
         im = (c0r * ai + c0i * ar) + (c1r * bi + c1i * br);
     };
     if constexpr (MODE == 0) {
-        constexpr int P = 4;
+        constexpr int P = PER / 2;
         V a[P], b[P];
         uint64_t at[P];
         const uint64_t bit = uint64_t(1) << ub, pairs = units / 2;
 #pragma unroll
         for (int u = 0; u < P; ++u) {
-            const uint64_t p = ((uint64_t)blockIdx.x * P + u) * 256 + threadIdx.x;
+            const uint64_t p = ((uint64_t)wg * P + u) * 256 + threadIdx.x;
             at[u] = insert_zero(min(p, pairs - 1), ub);
             a[u] = load16<NT>(psi + at[u]);
             b[u] = load16<NT>(psi + (at[u] | bit));
         }
 #pragma unroll
         for (int u = 0; u < P; ++u) {
-            if (((uint64_t)blockIdx.x * P + u) * 256 + threadIdx.x >= pairs) break;
+            if (((uint64_t)wg * P + u) * 256 + threadIdx.x >= pairs) break;
             V x, y;
 #pragma unroll
             for (int k = 0; k < A; ++k) {
@@ -3423,9 +3440,9 @@ __global__ __launch_bounds__(256, 6) void k_gate1q(typename Unit<T>::type* __res
             store16<NT>(psi + (at[u] | bit), y);
         }
     } else {
-        constexpr int P = 8;
+        constexpr int P = PER;
         V a[P];
-        const uint64_t u0 = (uint64_t)blockIdx.x * P * 256 + threadIdx.x;
+        const uint64_t u0 = (uint64_t)wg * P * 256 + threadIdx.x;
 #pragma unroll
         for (int u = 0; u < P; ++u) a[u] = load16<NT>(psi + min(u0 + u * 256, units - 1));
 #pragma unroll
@@ -3466,16 +3483,18 @@ __global__ __launch_bounds__(256, 6) void k_gate1q(typename Unit<T>::type* __res
 // set are negated). hb0 < hb1: the set unit bits from 3 up (-1: none), which
 // select the units; lomask: set bits among unit bits 0..2, and odd: the
 // second amplitude of a complex64 unit only - these select inside whole lines.
-// spread: each XCD takes its own stretch of the state. Selecting every other
+// spread: each XCD takes its own stretch of the state, in the caches (see
+// tile_block) and, beyond them, for unit bit 7. Selecting every other
 // 2 KiB (unit bit 7) leaves half of the memory channels idle in one compact
 // stretch: 28 qubits complex64, T on qubit 8, 354 us spread over eight against
 // 546 us; any other bit is as fast or faster in memory order (T on qubit 27:
-// 350 against 374 us).
-template <typename T, bool NEG, bool NT>
+// 350 against 374 us). P units of a thread: 8, and 2 in the caches for more
+// wavefronts (24 qubits complex128, T on qubit 0: 73 against 78 us).
+template <typename T, bool NEG, bool NT, int P>
 __global__ __launch_bounds__(256, 6) void k_phase(typename Unit<T>::type* __restrict__ psi, int hb0, int hb1, int lomask,
                                                int odd, int spread, T cr, T ci, uint64_t count) {
     using V = typename Unit<T>::type;
-    constexpr int A = Unit<T>::AMPS, P = 8;
+    constexpr int A = Unit<T>::AMPS;
     V a[P];
     uint64_t at[P];
     const uint64_t u0 = (uint64_t)(spread ? xcd_block() : blockIdx.x) * P * 256 + threadIdx.x;
@@ -4664,12 +4683,11 @@ hipError_t launch_gate1q_t(void* psi, int n, int q, const double m[8], hipStream
         hipLaunchKernelGGL(kern, dim3((unsigned)((units + per_group - 1) / per_group)), dim3(256), 0, st, p, ub, g,
                            units);
     };
-    // eight units per thread either way
-    if (ub >= 3) go(k_gate1q<T, 0, NT>, 2048);
-    else if (ub == 2) go(k_gate1q<T, 3, NT>, 2048);
-    else if (ub == 1) go(k_gate1q<T, 2, NT>, 2048);
-    else if (ub == 0) go(k_gate1q<T, 1, NT>, 2048);
-    else if constexpr (U::BITS == 1) go(k_gate1q<T, 4, NT>, 2048);
+    if (ub >= 3) go(k_gate1q<T, 0, NT>, 256 * gate1q_units(0, NT));
+    else if (ub == 2) go(k_gate1q<T, 3, NT>, 256 * gate1q_units(3, NT));
+    else if (ub == 1) go(k_gate1q<T, 2, NT>, 256 * gate1q_units(2, NT));
+    else if (ub == 0) go(k_gate1q<T, 1, NT>, 256 * gate1q_units(1, NT));
+    else if constexpr (U::BITS == 1) go(k_gate1q<T, 4, NT>, 256 * gate1q_units(4, NT));
     return hipGetLastError();
 }
 
@@ -4686,11 +4704,15 @@ hipError_t launch_phase_t(void* psi, int n, int q0, int q1, double cs, double sn
         else hb[nh++] = ub;
     }
     const uint64_t count = uint64_t(1) << (n - U::BITS - nh);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)((count + 2047) / 2048)), dim3(256), 0, st, (typename U::type*)psi,
-                           hb[0], hb[1], lomask, odd, hb[0] == 7 || hb[1] == 7, (T)cs, (T)sn, count);
+    const int spread = !beyond_caches(n, sizeof(T) == 8) || hb[0] == 7 || hb[1] == 7;
+    auto go = [&](auto kern, int per_thread) {
+        const unsigned per_group = 256 * per_thread;
+        hipLaunchKernelGGL(kern, dim3((unsigned)((count + per_group - 1) / per_group)), dim3(256), 0, st,
+                           (typename U::type*)psi, hb[0], hb[1], lomask, odd, spread, (T)cs, (T)sn, count);
     };
-    beyond_caches(n - nh, sizeof(T) == 8) ? go(k_phase<T, NEG, true>) : go(k_phase<T, NEG, false>);
+    if (beyond_caches(n - nh, sizeof(T) == 8)) go(k_phase<T, NEG, true, 8>, 8);
+    else if (beyond_caches(n, sizeof(T) == 8)) go(k_phase<T, NEG, false, 8>, 8);
+    else go(k_phase<T, NEG, false, 2>, 2);
     return hipGetLastError();
 }
 }  // namespace
