@@ -133,6 +133,8 @@ def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print, lr_
 def cmd_train(args):
     d = np.load(args.data, allow_pickle=False)
     x, y, meta = d["x"], d["y"], d["meta"]
+    keep = meta[:, 1] >= args.n_min
+    x, y, meta = x[keep], y[keep], meta[keep]
     held = meta[:, 0] % 5 == 4  # every fifth seed is validation
     mean = x[~held].mean(0)
     std = x[~held].std(0)
@@ -141,7 +143,7 @@ def cmd_train(args):
     xn = ((x - mean) / std).astype(np.float32)
     yn = ((y - y_mean) / y_std).astype(np.float32)
     params, hist = train(xn[~held], yn[~held], steps=args.steps, batch=args.batch, lr=args.lr,
-                         lr_end=args.lr_end, val=(xn[held], yn[held]))
+                         lr_end=args.lr_end, seed=args.seed, val=(xn[held], yn[held]))
     # validation error in log space -> typical relative error of a time prediction
     pred = qsim.mlp_predict_host(params, N_IN, N_HIDDEN, xn[held]) * y_std + y_mean
     rmse = float(np.sqrt(np.mean((pred - y[held]) ** 2)))
@@ -241,6 +243,8 @@ def main(argv=None):
     t.add_argument("--steps", type=int, default=4000)
     t.add_argument("--batch", type=int, default=512)
     t.add_argument("--lr", type=float, default=2e-3)
+    t.add_argument("--seed", type=int, default=0)
+    t.add_argument("--n-min", type=int, default=1, help="leave out the records of smaller states")
     t.add_argument("--lr-end", type=float, default=0.1, help="last learning rate over the first")
     t.add_argument("--out", required=True)
     c = sub.add_parser("compare")

@@ -19,8 +19,9 @@ def buffer(count, dtype, offset, gen):
     return torch.view_as_complex(v)[offset:]
 
 
-# 16 to 18 qubits: both sides of the runs (from 2^17 units of two fp32 or one amplitude)
-@pytest.mark.parametrize("n", [1, 2, 9, 16, 17, 18, 26])
+# 11 to 14 qubits: one work-group alone (up to 2^12 units of two fp32 or one amplitude), single
+# rounds and runs there; 16 to 18: both sides of the runs of many (from 2^17 units)
+@pytest.mark.parametrize("n", [1, 2, 9, 10, 11, 12, 13, 14, 16, 17, 18, 26])
 @pytest.mark.parametrize("dt,out_dt,ref_dt,offset", [
     (torch.complex64, torch.float32, torch.complex64, 0), (torch.complex64, torch.float32, torch.complex64, 1),
     (torch.complex64, torch.float64, torch.complex128, 0), (torch.complex64, torch.float64, torch.complex128, 1),
