@@ -99,10 +99,9 @@ def init_params(rng, n_in=N_IN, h=N_HIDDEN):
                            np.zeros(1)]).astype(np.float32)
 
 
-def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print, lr_end=0.1):
+def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print):
     """Train on the GPU with the library's kernels. x: [N, in] normalised
-    float32, y: [N] normalised. The rate falls along a half cosine from lr to
-    lr * lr_end. Returns (params, history)."""
+    float32, y: [N] normalised. Returns (params, history)."""
     import torch
     dev = torch.device("cuda")
     rng = np.random.default_rng(seed)
@@ -118,7 +117,7 @@ def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print, lr_
         xb = xt.index_select(0, idx).contiguous()
         yb = yt.index_select(0, idx).contiguous()
         grad, loss = qsim.mlp_backward(p, N_IN, N_HIDDEN, xb, yb)
-        cur_lr = lr * (0.5 * (1 + math.cos(math.pi * step / steps)) * (1 - lr_end) + lr_end)
+        cur_lr = lr * (0.5 * (1 + math.cos(math.pi * step / steps)) * 0.9 + 0.1)
         qsim.mlp_adam(p, grad, m, v, step, cur_lr)
         if step % max(1, steps // 10) == 0 or step == 1:
             rec = {"step": step, "train_mse": float(loss.item())}
@@ -133,8 +132,6 @@ def train(x, y, steps=4000, batch=512, lr=2e-3, seed=0, val=None, log=print, lr_
 def cmd_train(args):
     d = np.load(args.data, allow_pickle=False)
     x, y, meta = d["x"], d["y"], d["meta"]
-    keep = meta[:, 1] >= args.n_min
-    x, y, meta = x[keep], y[keep], meta[keep]
     held = meta[:, 0] % 5 == 4  # every fifth seed is validation
     mean = x[~held].mean(0)
     std = x[~held].std(0)
@@ -142,8 +139,7 @@ def cmd_train(args):
     y_mean, y_std = float(y[~held].mean()), float(y[~held].std())
     xn = ((x - mean) / std).astype(np.float32)
     yn = ((y - y_mean) / y_std).astype(np.float32)
-    params, hist = train(xn[~held], yn[~held], steps=args.steps, batch=args.batch, lr=args.lr,
-                         lr_end=args.lr_end, seed=args.seed, val=(xn[held], yn[held]))
+    params, hist = train(xn[~held], yn[~held], steps=args.steps, val=(xn[held], yn[held]))
     # validation error in log space -> typical relative error of a time prediction
     pred = qsim.mlp_predict_host(params, N_IN, N_HIDDEN, xn[held]) * y_std + y_mean
     rmse = float(np.sqrt(np.mean((pred - y[held]) ** 2)))
@@ -241,11 +237,6 @@ def main(argv=None):
     t = sub.add_parser("train")
     t.add_argument("--data", required=True)
     t.add_argument("--steps", type=int, default=4000)
-    t.add_argument("--batch", type=int, default=512)
-    t.add_argument("--lr", type=float, default=2e-3)
-    t.add_argument("--seed", type=int, default=0)
-    t.add_argument("--n-min", type=int, default=1, help="leave out the records of smaller states")
-    t.add_argument("--lr-end", type=float, default=0.1, help="last learning rate over the first")
     t.add_argument("--out", required=True)
     c = sub.add_parser("compare")
     c.add_argument("--n", default="28,29,30")
