@@ -78,15 +78,12 @@ def kernel_name(rec, k6_kernel=2, pair_tile=11, dbl=False, n=None) -> str:
             return "k_cluster_f32_split7<%s, %s, %s>" % (b(lowt), b(rec.get("stats")),
                                                          b(far and first(1, 4) and not rec.get("stats")))
         return "k_cluster_f32_split7<%s, %s>" % (b(lowt), b(rec.get("stats")))
-    if n is not None and k6_kernel == 2 and (k == 6 or k == 5 and n >= 11 or k == 4 and far):
-        # 4 and 5 qubits are padded to 6, with qubits above the lowest five others
+    if n is not None and k6_kernel == 2 and k == 6:
         if rec.get("staged"):
             return "k_cluster_f32_split6s<%s, %s>" % (b(lowt), b(far))
         if rec.get("stats"):
             return "k_cluster_f32_split6_sum<%s>" % b(lowt)
-        own = rec["qubits"][:k]
-        pads = [q for q in range(n) if q not in own][5:5 + 6 - k]
-        return "k_cluster_f32_split6<%s, %s>" % (b(lowt), b(far and sorted(own + pads)[1] >= 4))
+        return "k_cluster_f32_split6<%s, %s>" % (b(lowt), b(far and first(1, 4)))
     if k == 6 and k6_kernel in (1, 2):
         if k6_kernel == 2 and rec.get("staged"):
             return "k_cluster_f32_split6s<%s>" % b(lowt)

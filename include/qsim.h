@@ -281,10 +281,8 @@ qsim_status qsim_op_timings(qsim_state s, int32_t* op_kind, int32_t* op_k, int32
  * of 6-qubit clusters on complex64 states: 0 the fp32 real-split product, 1
  * the fp32 three-multiplication complex product, 2 (default) fp16 matrix
  * cores on hi / lo halves of the operands (about 2^-21 relative error, the
- * size of fp32 rounding), which then also takes 5-qubit clusters and, on
- * states of 512 MiB and more, 4-qubit ones, padded with identity qubits; only
- * with 2 are 7-qubit clusters formed (the same halves on the matrix's real
- * and imaginary parts),
+ * size of fp32 rounding); only with 2 are 7-qubit clusters formed (the same
+ * halves on the matrix's real and imaginary parts),
  * read when a cluster is enqueued. QSIM_OPT_FOLD_INIT (default 2): when a
  * run starts from the uniform state (skip_initial_h) with a cluster, 1
  * writes that state and the cluster - a product state again - in one pass

@@ -254,8 +254,6 @@ struct Chunk {
         int variant;     // kind 0: matrix-core kernel variant chosen by the learned model, -1: the library's rule
         int omask, rmask;  // kind 8: the table form's shared and sign-flipped rows, omask -1: matrix cores
         int slot3;         // kind 8 table form: the table's slot
-        int k;             // kind 0: the cluster's own qubits (geom has those its matrix is padded to)
-        int qubits[kMaxK];
     };
     std::vector<Item> items;
     int slots_used = 0;
@@ -361,8 +359,8 @@ qsim_status flush(qsim_state_s* s, Chunk& c) {
         const int variant =
             it.kind == 0 ? (it.variant >= 0 ? it.variant : cluster_variant_for(s->dbl, it.geom, it.layout)) : 0;
         if (it.kind == 0 || it.kind == 6 || it.kind == 7 || it.kind == 8) {
-            r.k = it.kind == 0 ? it.k : it.geom.k;
-            for (int j = 0; j < r.k; ++j) r.qubits[j] = it.kind == 0 ? it.qubits[j] : it.geom.t[j];
+            r.k = it.geom.k;
+            for (int j = 0; j < it.geom.k; ++j) r.qubits[j] = it.geom.t[j];
             r.flags = (it.epi >= 0 ? 1 : 0) | (variant == 1 ? 2 : 0) | (it.layout != LAYOUT_PLAIN ? 4 : 0) |
                       (it.stats ? 8 : 0) | (it.kind == 8 && it.omask >= 0 ? 16 : 0) | (std::min(it.n_epi, 255) << 8);
         } else if (it.kind >= 2) {
@@ -455,40 +453,16 @@ qsim_status add_cluster(qsim_state_s* s, Chunk& c, int k, const int* qubits, con
         qsim_status r = flush(s, c);
         if (r != QSIM_OK) return r;
     }
-    int layout = fold_init ? LAYOUT_PLAIN : cluster_layout(s->dbl, k, s->n);
-    if (layout < 0) return fail(QSIM_E_UNSUPPORTED, "no kernel for a cluster of this width on this state");
-    // clusters of 4 and 5 qubits on the 6-qubit fp16-halves kernel: identity on
-    // the lowest qubits above the five column bits of its tile, which leaves the
-    // tile's contiguous runs as they are (a workspace with slots too small for a
-    // 6-qubit matrix keeps the fp32 kernels). The added qubits take the matrix
-    // index bits from 2 up, which number the kernel's product steps: the zero
-    // entries of the padded matrix then fill whole steps, and a row is rounded
-    // as often as a 4- or 5-qubit product has steps (error of a random 4- / 5-
-    // qubit gate: 1.0e-7 / 1.17e-7 of the norm, fp32 matrix cores 1.06e-7 /
-    // 1.47e-7; with the zeros spread over the steps up to 1.46e-7).
-    int t[kMaxK], kt = k;
-    for (int j = 0; j < k; ++j) t[j] = qubits[j];
-    if (layout == LAYOUT_SPLIT16F && k < 6) {
-        if (s->kmax_ws >= 6) {
-            uint64_t own = 0;
-            for (int j = 0; j < k; ++j) own |= uint64_t(1) << qubits[j];
-            kt = 2;
-            for (int b = 0, free = 0; b < s->n && kt < 2 + 6 - k; ++b)
-                if (!(own >> b & 1) && ++free > 5) t[kt++] = b;
-            for (int j = 2; j < k; ++j) t[kt++] = qubits[j];
-        } else {
-            layout = LAYOUT_MFMA32F;
-        }
-    }
     int pos_of[64];
     for (int i = 0; i < 64; ++i) pos_of[i] = -1;
-    for (int j = 0; j < kt; ++j) pos_of[t[j]] = j;
+    for (int j = 0; j < k; ++j) pos_of[qubits[j]] = j;
     BuildOp bo;
     std::memset(&bo, 0, sizeof(bo));
-    bo.k = kt;
+    bo.k = k;
     bo.gate0 = (int)c.bgates.size();
     bo.is_double = fold_init ? 1 : s->dbl;
-    bo.layout = layout;
+    bo.layout = fold_init ? LAYOUT_PLAIN : cluster_layout(s->dbl, k, s->n);
+    if (bo.layout < 0) return fail(QSIM_E_UNSUPPORTED, "no kernel for a cluster of this width on this state");
     bo.out_off = (int64_t)c.slots_used * (int64_t)slot_bytes(s->dbl, s->kmax_ws);
     for (int gi : members) c.bgates.push_back(to_build_gate(gates[gi], pos_of, c.dense));
     // epilogue: terms on target qubits only join the matrix, the rest go to the descriptor
@@ -499,9 +473,7 @@ qsim_status add_cluster(qsim_state_s* s, Chunk& c, int k, const int* qubits, con
     Chunk::Item it;
     std::memset(&it, 0, sizeof(it));
     it.kind = fold_init ? 6 : 0;
-    it.k = k;
-    for (int j = 0; j < k; ++j) it.qubits[j] = qubits[j];
-    set_geom(it.geom, s->n, kt, t);
+    set_geom(it.geom, s->n, k, qubits);
     it.layout = bo.layout;
     it.slot = c.slots_used++;
     it.epi = -1;

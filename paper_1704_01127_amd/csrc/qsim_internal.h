@@ -97,8 +97,7 @@ enum : int32_t {
     LAYOUT_MFMA32F = 1,   // real-split, permuted for v_mfma_f32_32x32x2_f32
     LAYOUT_MFMA16D = 2,   // real-split, permuted for v_mfma_f64_16x16x4_f64
     LAYOUT_GAUSS32F = 3,  // k = 6 float: Re M, Im M, Re M + Im M (three-product complex matrix)
-    LAYOUT_SPLIT16F = 4,  // k = 6 float (5, and 4 beyond the caches, padded to 6): fp16 hi / lo halves of 16 x
-                          // the real-split matrix
+    LAYOUT_SPLIT16F = 4,  // k = 6 float: fp16 hi / lo halves of 16 x the real-split matrix
     LAYOUT_SPLIT7 = 5     // k = 7 float: fp16 hi / lo halves of 16 x Re M and 16 x Im M
 };
 
@@ -118,20 +117,13 @@ constexpr int64_t kTicketOff7 = 4 * 128 * 128 * 2;
 
 // Geometry of one cluster application.
 struct ClusterGeom {
-    int32_t t[kMaxK];   // target qubits: bit j of the matrix index is qubit t[j]
-    int32_t srt[kMaxK]; // the same, ascending (where the column bits leave gaps)
+    int32_t t[kMaxK];   // sorted target qubits
     int32_t n;          // qubits of the state
     int32_t k;
     uint64_t ncols;     // 2^(n-k)
 };
 inline void set_geom(ClusterGeom& g, int n, int k, const int* t) {
-    for (int j = 0; j < kMaxK; ++j) g.t[j] = g.srt[j] = j < k ? t[j] : 0;
-    for (int i = 1; i < k; ++i)
-        for (int j = i; j > 0 && g.srt[j] < g.srt[j - 1]; --j) {
-            const int32_t x = g.srt[j];
-            g.srt[j] = g.srt[j - 1];
-            g.srt[j - 1] = x;
-        }
+    for (int j = 0; j < kMaxK; ++j) g.t[j] = j < k ? t[j] : 0;
     g.n = n;
     g.k = k;
     g.ncols = uint64_t(1) << (n - k);

@@ -59,7 +59,7 @@ __device__ __forceinline__ uint64_t insert_zero(uint64_t c, int t) {
 template <int K>
 __device__ __forceinline__ uint64_t deposit_cols(uint64_t c, const ClusterGeom& g) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) c = insert_zero(c, g.srt[j]);
+    for (int j = 0; j < K; ++j) c = insert_zero(c, g.t[j]);
     return c;
 }
 
@@ -4403,15 +4403,12 @@ int cluster_layout(bool dbl, int k, int n) {
             if (n - k < 5) return LAYOUT_PLAIN;
             return g_k6_kernel == 2 ? LAYOUT_SPLIT16F : (g_k6_kernel == 1 ? LAYOUT_GAUSS32F : LAYOUT_MFMA32F);
         }
-        if (k < 4 || n - k < 6) return LAYOUT_PLAIN;
-        // On the 6-qubit halves kernel, padded (the caller does), where its tile
-        // fits: the fp32 matrix cores hold a 5-qubit pass back at every size (30
-        // qubits, mean of 23 target sets: 3.03 ms padded against 3.49; 24 qubits:
-        // 52 us against 65-73; 20 qubits: 10 us either way), a 4-qubit one only
-        // beyond the caches (30 qubits: 3.12 against 3.40 ms, 24 qubits: 52
-        // against 46 us). The halves' error is not larger (measured where the
-        // padding is laid out).
-        return g_k6_kernel == 2 && n >= 11 && (k == 5 || beyond_caches(n, false)) ? LAYOUT_SPLIT16F : LAYOUT_MFMA32F;
+        // 4 and 5 qubits: the fp32 matrix cores at every size. The 6-qubit fp16-halves
+        // kernel, the cluster padded with identity qubits, took 3.03 against 3.49 ms
+        // for 5 qubits at 30 (24 qubits: 52 against 65-73 us), but a matrix entry above
+        // 4094 overflows its halves, a matrix scaled by 1e-6 comes out wrong by 9e-3,
+        // and columns that differ in a padding qubit share one scale.
+        return (k >= 4 && n - k >= 6) ? LAYOUT_MFMA32F : LAYOUT_PLAIN;
     }
     const int nb = (k == 6) ? 1 : 2;
     return (k >= 3 && n - k >= 4 + (nb == 2)) ? LAYOUT_MFMA16D : LAYOUT_PLAIN;
