@@ -1088,10 +1088,12 @@ qsim_status qsim_run_circuit(qsim_state s, const qsim_gate* gates, int n_gates, 
             st.n_diag_ops++;
         } else {
             r = add_cluster(s, c, op.k, op.qubits, gates, op.members, op.epi);
-            if (r == QSIM_OK && learned_variants) {  // the variant the model predicts faster for these targets
-                int v = -1;
-                learned_cost_best_us(s->n, s->dbl, op.k, op.qubits, (int)op.epi.size(), &v);
-                c.items.back().variant = v;
+            if (r == QSIM_OK && learned_variants) {
+                // the variant the model predicts faster for these targets, the table's where it
+                // leaves the choice to it: a choice either way, which gives way to the sums below
+                Chunk::Item& it = c.items.back();
+                learned_cost_best_us(s->n, s->dbl, op.k, op.qubits, (int)op.epi.size(), &it.variant);
+                if (it.variant < 0) it.variant = cluster_variant_for(s->dbl, it.geom, it.layout);
             }
             st.n_clusters_by_k[op.k]++;
             st.n_gates_fused_epilogue += (int)op.epi.size();
@@ -1103,7 +1105,7 @@ qsim_status qsim_run_circuit(qsim_state s, const qsim_gate* gates, int n_gates, 
     // sums the quantities qsim_probs reports, so they need no further pass
     if (opts && opts->fused_stats && !c.items.empty()) {
         Chunk::Item& last = c.items.back();
-        // the sums come from the direct kernels: a staged choice of the model
+        // the sums come from the direct kernels: a staged choice of a learned run
         // gives way, since the sums save a whole pass over the state
         const ClusterGeom& lg = last.geom;
         if (last.kind == 0 && last.variant == 1 && cluster_stats_supported(s->dbl, lg.n, lg.k, last.layout, 0))
