@@ -4557,8 +4557,10 @@ hipError_t launch_cluster(void* psi, bool dbl, const ClusterGeom& g, const void*
         const uint64_t tiles = g.ncols / 32;
         const unsigned grid = grid_for(tiles, 4, kSplit7Grid);
         // the tile counters behind the matrix, which its builder zeroes (a pass
-        // over a state this large has a full grid and a multiple of 8 tiles)
-        uint32_t* tickets = beyond_caches(g.n, false)
+        // over a state this large has a full grid and a multiple of 8 tiles). A
+        // pass that takes the sums has none: which tiles a wave adds up would
+        // depend on the order in which the waves ask, and so the sums' last bits.
+        uint32_t* tickets = beyond_caches(g.n, false) && !stats_part
                                 ? reinterpret_cast<uint32_t*>(static_cast<char*>(const_cast<void*>(mat)) + kTicketOff7)
                                 : nullptr;
         auto go = [&](auto kern) {
