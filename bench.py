@@ -45,9 +45,10 @@ def kernel_name(rec, k6_kernel=2, pair_tile=11, dbl=False, n=None) -> str:
     the state's qubits, which decide the kernel's form; without it the kernel's
     plain name)."""
     k, lowt = rec["k"], rec["qubits"][0] == 0
-    staged_valu = n is not None and 2 <= k <= 3 and n - k >= 6 and not rec.get("mfma")
     # a state of 512 MiB and more: non-temporal accesses, where they cover whole 128-byte lines
     far = n is not None and n + (4 if dbl else 3) >= 29
+    staged_valu = n is not None and (1 if far and not rec.get("stats") else 2) <= k <= 3 and n - k >= 6 \
+        and not rec.get("mfma")
     b = lambda x: "true" if x else "false"  # noqa: E731
     first = lambda i, bits: len(rec["qubits"]) > i and rec["qubits"][i] >= bits  # noqa: E731
     if dbl:
@@ -66,7 +67,7 @@ def kernel_name(rec, k6_kernel=2, pair_tile=11, dbl=False, n=None) -> str:
     if rec["kind"] == "pair":
         q = set(rec["qubits"])
         ten = pair_tile == 10 and (0 in q or len(q) < 10)  # the 10-qubit tile holds qubit 0
-        return "k_cluster_f32_pair10<12>" if ten else "k_cluster_f32_multi<2, 8>"
+        return "k_cluster_f32_pair10<12>" if ten else "k_cluster_f32_multi<2, 8%s>" % (", true" if n is not None else "")
     if staged_valu and not far and not rec.get("stats"):
         return "k_cluster_valu_cached<float, %d>" % k
     if staged_valu:  # its second flag sums the reductions

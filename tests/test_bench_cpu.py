@@ -55,6 +55,56 @@ def test_kernel_names_of_launch_records():
     assert b.kernel_name(pair, pair_tile=10) == "k_cluster_f32_pair10<12>"
 
 
+def mangled(name):
+    """The start of a kernel's symbol, from its source name."""
+    base, args = name.rstrip(">").split("<")
+    code = {"float": "f", "double": "d", "true": "Lb1E", "false": "Lb0E"}
+    return base + "I" + "".join(code.get(a) or "Li%sE" % a for a in args.split(", ")) + "E"
+
+
+def test_names_with_the_state_size_are_the_library_kernels():
+    """With the state's size, every name is a kernel the library holds, and the
+    one its launcher takes on either side of 512 MiB of state."""
+    from paper_1704_01127_amd import qsim
+    b = _bench()
+    rec = lambda k, q, **f: dict(kind=f.pop("kind", "cluster"), k=k, qubits=q, **f)
+    with open(qsim.LIB_PATH, "rb") as f:
+        library = f.read()
+    low, high = [0, 1, 2, 3, 4, 5, 6], [4, 7, 9, 12, 15, 18, 20]
+    for dbl in (False, True):
+        for n in (22, 25, 26, 30):
+            for k in range(1, 8 - dbl):
+                for q in (low[:k], high[:k], [0] + high[:k - 1]):
+                    mfma = k >= (3 if dbl else 4)
+                    forms = [dict(mfma=mfma)]
+                    if mfma and k <= 6 - dbl:
+                        forms.append(dict(mfma=mfma, staged=True))
+                    if not dbl and k >= 2:
+                        forms.append(dict(mfma=mfma, stats=True))
+                    for form in forms:
+                        name = b.kernel_name(rec(k, q, **form), dbl=dbl, n=n)
+                        assert mangled(name).encode() in library, (name, n, k, q, form)
+    one = rec(1, [3])
+    assert b.kernel_name(one, n=25) == "k_cluster_valu<float, 1>"
+    assert b.kernel_name(one, n=26) == "k_cluster_valu_staged<float, 1, false>"
+    assert b.kernel_name(one, dbl=True, n=24) == "k_cluster_valu<double, 1>"
+    assert b.kernel_name(one, dbl=True, n=25) == "k_cluster_valu_staged<double, 1, false>"
+    assert b.kernel_name(rec(2, [3, 9]), n=25) == "k_cluster_valu_cached<float, 2>"
+    assert b.kernel_name(rec(4, high[:4], mfma=True, staged=True), n=30) == "k_cluster_f32_stage<4, 6, false>"
+    assert b.kernel_name(rec(5, low[:5], mfma=True, stats=True), n=30) == "k_cluster_f32_mfma<5, 2, true, true>"
+    assert b.kernel_name(rec(6, high[:6], mfma=True), n=25) == "k_cluster_f32_split6<false, false>"
+    assert b.kernel_name(rec(6, high[:6], mfma=True), n=26) == "k_cluster_f32_split6<false, true>"
+    assert b.kernel_name(rec(6, low[:6], mfma=True), n=26) == "k_cluster_f32_split6<true, false>"  # partial lines
+    assert b.kernel_name(rec(6, low[:6], mfma=True, staged=True), n=26) == "k_cluster_f32_split6s<true, true>"
+    assert b.kernel_name(rec(6, low[:6], mfma=True, stats=True), n=26) == "k_cluster_f32_split6_sum<true>"
+    assert b.kernel_name(rec(7, high, mfma=True), n=26) == "k_cluster_f32_split7<false, false, true>"
+    assert b.kernel_name(rec(7, high, mfma=True, stats=True), n=26) == "k_cluster_f32_split7<false, true, false>"
+    assert b.kernel_name(rec(5, high[:5], mfma=True, staged=True), dbl=True, n=25) == "k_cluster_f64_stage<5, 4, true>"
+    assert b.kernel_name(rec(5, high[:5], mfma=True), dbl=True, n=24) == "k_cluster_f64_mfma<5, 1, false>"
+    pair = rec(5, low + high[:3], kind="pair")
+    assert mangled(b.kernel_name(pair, n=30)).encode() in library
+
+
 def test_cpu_baseline_runs_the_whole_circuit():
     """The CPU-baseline leg runs the oracle over every gate of the circuit it
     is given (no sampling) and records the host it ran on."""
