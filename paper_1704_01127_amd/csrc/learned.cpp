@@ -85,24 +85,27 @@ size_t mlp_param_count(int n_in, int h) { return (size_t)h * n_in + h + (size_t)
 // chain keeps its order, so the result does not depend on the loop shape.
 // kInputFirst: W1 and W2 are stored with the input index first, as the loops
 // read them (the loaded model's; the public layout has the unit index first,
-// whose strided reads took most of a prediction's time).
-template <bool kHwFma, bool kInputFirst>
-static float mlp_forward_impl(const float* p, int n_in, int h, const float* x) {
+// whose strided reads took most of a prediction's time). H: the number of
+// units, 0 where only h tells it; a known one keeps the units in registers
+// (64 units: 0.58 us a prediction instead of 1.13).
+template <bool kHwFma, bool kInputFirst, int H = 0>
+static float mlp_forward_impl(const float* p, int n_in, int h_any, const float* x) {
+    const int h = H ? H : h_any;
     const float* W1 = p;
     const float* b1 = W1 + (size_t)h * n_in;
     const float* W2 = b1 + h;
     const float* b2 = W2 + (size_t)h * h;
     const float* W3 = b2 + h;
     const float* b3 = W3 + h;
-    float a1[256], a2[256];
+    float a1[H ? H : 256], a2[H ? H : 256];
     for (int i = 0; i < h; ++i) a1[i] = b1[i];
     for (int j = 0; j < n_in; ++j)
-        for (int i = 0; i < h; ++i) 
+        for (int i = 0; i < h; ++i)
             a1[i] = std::fma(kInputFirst ? W1[(size_t)j * h + i] : W1[(size_t)i * n_in + j], x[j], a1[i]);
     for (int i = 0; i < h; ++i) a1[i] = a1[i] > 0.f ? a1[i] : 0.f;
     for (int i = 0; i < h; ++i) a2[i] = b2[i];
     for (int j = 0; j < h; ++j)
-        for (int i = 0; i < h; ++i) 
+        for (int i = 0; i < h; ++i)
             a2[i] = std::fma(kInputFirst ? W2[(size_t)j * h + i] : W2[(size_t)i * h + j], a1[j], a2[i]);
     for (int i = 0; i < h; ++i) a2[i] = a2[i] > 0.f ? a2[i] : 0.f;
     float y = b3[0];
@@ -114,7 +117,8 @@ static float mlp_forward_impl(const float* p, int n_in, int h, const float* x) {
 // library call.
 template <bool kInputFirst>
 __attribute__((target("avx2,fma"))) static float mlp_forward_fma(const float* p, int n_in, int h, const float* x) {
-    return mlp_forward_impl<true, kInputFirst>(p, n_in, h, x);
+    return h == 64 ? mlp_forward_impl<true, kInputFirst, 64>(p, n_in, h, x)
+                   : mlp_forward_impl<true, kInputFirst>(p, n_in, h, x);
 }
 
 template <bool kInputFirst>

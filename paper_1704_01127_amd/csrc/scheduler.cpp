@@ -787,17 +787,21 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
     const Dag dag(n, gates, S.dropped);
     // candidate qubit sets (dense sets of the interaction graph, two slacks)
     std::vector<uint64_t> sets0, sets1;
-    if (o.cluster_sets && kmax >= 2) dense_sets(n, gates, S.dropped, kmax, sets0, sets1);
+    auto find_sets = [&]() {
+        if (o.cluster_sets && kmax >= 2) dense_sets(n, gates, S.dropped, kmax, sets0, sets1);
+    };
     // with a two-cluster folded start and clusters wider than 6, candidates
     // whose first two clusters have at most 6 qubits are built as well
     const int fold = S.uniform_init ? o.fold_start : 0;
     const int first_caps = (fold >= 2 && kmax > 6) ? 2 : 1;
     // the one-deviation schedules of the widest cap, with the larger family of
     // sets (slack 1: it holds the slack-0 sets)
-    const std::vector<uint64_t>* dev_sets = sets1.empty() ? &sets0 : &sets1;
-    const bool deviations =
-        o.deviations && o.parallel && o.cluster_sets && n >= kDevMinQubits && kmax >= 2 && !dev_sets->empty();
+    auto dev_family = [&]() { return sets1.empty() ? &sets0 : &sets1; };
+    const bool may_deviate = o.deviations && o.parallel && o.cluster_sets && n >= kDevMinQubits && kmax >= 2;
     if (o.mode == 1 || !cost) {
+        find_sets();
+        const std::vector<uint64_t>* dev_sets = dev_family();
+        const bool deviations = may_deviate && !dev_sets->empty();
         // the greedy schedules with and without the candidate sets (and with
         // a 6-qubit start); the one with the fewest passes wins, the start
         // counted as the write-only pass it becomes (ties: the earlier)
@@ -866,12 +870,19 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
         for (auto& q : sets) c += cost(k, q, 0);
         return c / 4;
     };
-    const double full_per_qubit = typical(kmax) / kmax;
-    const bool cd_deviations = deviations && (kmax < 2 || full_per_qubit <= typical(kmax - 1) / (kmax - 1));
+    double per_qubit[kMaxK + 1] = {};
+    for (int kc = k_lo; kc <= kmax; ++kc) per_qubit[kc] = typical(kc) / kc;
+    bool cd_deviations = may_deviate && per_qubit[kmax] <= per_qubit[kmax - 1];
+    // The widest cap's sets are found before the candidates where several need
+    // them, else beside the others, inside their own tasks
+    const bool sets_first = !o.parallel || first_caps > 1 || cd_deviations;
+    if (sets_first) find_sets();
+    const std::vector<uint64_t>* dev_sets = dev_family();
+    cd_deviations = cd_deviations && !dev_sets->empty();
     // narrower caps expected to pay (a cheaper cluster per qubit): their
     // gated candidates start with the others instead of in a second round
     bool narrow_likely = false;
-    for (int kc = k_lo; kc < kmax; ++kc) narrow_likely |= typical(kc) / kc < full_per_qubit;
+    for (int kc = k_lo; kc < kmax; ++kc) narrow_likely |= per_qubit[kc] < per_qubit[kmax];
     auto priced = [&](std::vector<SOp> ops) {
         double total = 0.0, c0 = 0.0, c1 = 0.0;
         for (size_t i = 0; i < ops.size(); ++i) {
@@ -939,12 +950,12 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
     if (kmax > 1)
         add(kmax - 1,
             [&]() { return priced(greedy_ops(dag, gates, S.n_applied, kmax, o.fuse_diag, &cost)); });
-    // set families: kmax's are at hand; a narrower cap's are found inside
-    // its tasks, one task per (cap, slack)
+    // set families: kmax's may be at hand; the others are found inside their
+    // tasks, one task per (cap, slack)
     if (o.cluster_sets)
         for (int kc = std::max(2, k_lo); kc <= kmax; ++kc)
             for (int slack = 0; slack < 2; ++slack) {
-                if (kc == kmax) {
+                if (kc == kmax && sets_first) {
                     const std::vector<uint64_t>* fs = slack ? &sets1 : &sets0;
                     if (fs->empty()) continue;
                     add(
@@ -955,13 +966,16 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
                         },
                         1);
                 } else {
-                    add(kc, [&, kc, slack]() {
-                        std::vector<uint64_t> a, b;
-                        dense_sets(n, gates, S.dropped, kc, a, b);
-                        const std::vector<uint64_t>& sets = slack ? b : a;
-                        if (sets.empty()) return Cand(std::vector<SOp>(), -1.0);  // no such family: not a candidate
-                        return priced(greedy_ops(dag, gates, S.n_applied, kc, o.fuse_diag, nullptr, &sets));
-                    });
+                    add(
+                        kc == kmax ? 0 : kc,
+                        [&, kc, slack]() {
+                            std::vector<uint64_t> a, b;
+                            dense_sets(n, gates, S.dropped, kc, a, b);
+                            const std::vector<uint64_t>& sets = slack ? b : a;
+                            if (sets.empty()) return Cand(std::vector<SOp>(), -1.0);  // no such family: not a candidate
+                            return priced(greedy_ops(dag, gates, S.n_applied, kc, o.fuse_diag, nullptr, &sets));
+                        },
+                        1);
                 }
             }
     // First every ungated candidate (in parallel: all of them at once, with
@@ -986,10 +1000,10 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
         for (size_t i = nplain; i < fns.size(); ++i)
             if (rest[i]) res[i] = std::move(more[i]);
     }
-    double passes = 0.0;  // fewest passes of the other candidates
+    double passes = 0.0;  // fewest passes of the candidates without a deviation
     bool any = false;
     for (size_t i = 0; i < fns.size(); ++i)
-        if (want[i] && gate[i] >= 0 && res[i].second >= 0) {
+        if (cd_deviations && want[i] && gate[i] >= 0 && res[i].second >= 0) {
             const double p = effective_passes(res[i].first, gates, fold);
             if (!any || p < passes) passes = p;
             any = true;
@@ -1006,9 +1020,9 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
     double best_cost = -1.0;
     for (const Cand& cand : cands)
         if (cand.second >= 0 && (best_cost < 0 || cand.second < best_cost)) best_cost = cand.second;
-    const Cand* best = nullptr;
+    Cand* best = nullptr;
     double best_passes = 0.0;
-    for (const Cand& cand : cands) {
+    for (Cand& cand : cands) {
         if (cand.second < 0 || cand.second > best_cost * kSameCost) continue;
         const double p = effective_passes(cand.first, gates, fold);
         if (!best || p < best_passes || (p == best_passes && cand.second < best->second)) {
@@ -1016,7 +1030,7 @@ Schedule make_schedule(int n, const std::vector<SGate>& gates, const SchedOpts& 
             best_passes = p;
         }
     }
-    if (best) S.ops = best->first;
+    if (best) S.ops = std::move(best->first);
     return S;
 }
 
