@@ -3480,16 +3480,17 @@ __global__ __launch_bounds__(256, 6) void k_gate1q(typename Unit<T>::type* __res
 
 // Diagonal gates of the plain method: diag(1, e^{i phi}) on one qubit (only
 // amplitudes with its bit set change) or CZ (NEG: amplitudes with both bits
-// set are negated). hb0 < hb1: the set unit bits from 3 up (-1: none), which
-// select the units; lomask: set bits among unit bits 0..2, and odd: the
-// second amplitude of a complex64 unit only - these select inside whole lines.
+// set are negated). hb0 < hb1: the set unit bits that select the units (-1:
+// none), all from 3 up, from 2 in the caches; lomask: set bits among the lower
+// ones, and odd: the second amplitude of a complex64 unit only - these select
+// among the units that are moved.
 // spread: each XCD takes its own stretch of the state, in the caches (see
 // tile_block) and, beyond them, for unit bit 7. Selecting every other
 // 2 KiB (unit bit 7) leaves half of the memory channels idle in one compact
 // stretch: 28 qubits complex64, T on qubit 8, 354 us spread over eight against
 // 546 us; any other bit is as fast or faster in memory order (T on qubit 27:
-// 350 against 374 us). P units of a thread: 8, and 2 in the caches for more
-// wavefronts (24 qubits complex128, T on qubit 0: 73 against 78 us).
+// 350 against 374 us). P: units of a thread (24 qubits complex128, T on qubit 0:
+// 73 us with 2, 78 with 8).
 template <typename T, bool NEG, bool NT, int P>
 __global__ __launch_bounds__(256, 6) void k_phase(typename Unit<T>::type* __restrict__ psi, int hb0, int hb1, int lomask,
                                                int odd, int spread, T cr, T ci, uint64_t count) {
@@ -4691,26 +4692,41 @@ hipError_t launch_gate1q_t(void* psi, int n, int q, const double m[8], hipStream
 }
 
 // A phase (or, NEG, a sign) on the amplitudes whose bits q0 (and q1 >= 0) are set.
+// Where the selected units fit the caches, unit bit 2 selects too: half lines are
+// enough there (T on qubit 3, complex64: 24 qubits 30 us, whole lines 39; 26 qubits
+// 162 and 174), while HBM moves whole lines anyway (27 qubits: 404 us half lines,
+// 357 whole). Units of a thread: 8 from HBM and on half lines, else 2 for more
+// wavefronts, and 1 for a selection of a larger state (26 qubits, T on the highest:
+// 74 us; 8 units in memory order 79).
 template <typename T, bool NEG>
 hipError_t launch_phase_t(void* psi, int n, int q0, int q1, double cs, double sn, hipStream_t st) {
     using U = Unit<T>;
-    int hb[2] = {-1, -1}, nh = 0, lomask = 0, odd = 0;
-    for (int q : {std::min(q0, q1), std::max(q0, q1)}) {
-        const int ub = q - U::BITS;
-        if (q < 0) continue;
-        if (ub < 0) odd = 1;
-        else if (ub < 3) lomask |= 1 << ub;
-        else hb[nh++] = ub;
-    }
+    constexpr bool dbl = sizeof(T) == 8;
+    int hb[2], nh, lomask, odd;
+    auto select = [&](int lowest) {  // unit bits from `lowest` up select units, lower ones inside them
+        hb[0] = hb[1] = -1;
+        nh = lomask = odd = 0;
+        for (int q : {std::min(q0, q1), std::max(q0, q1)}) {
+            const int ub = q - U::BITS;
+            if (q < 0) continue;
+            if (ub < 0) odd = 1;
+            else if (ub < lowest) lomask |= 1 << ub;
+            else hb[nh++] = ub;
+        }
+    };
+    select(2);
+    const bool nt = beyond_caches(n - nh, dbl);
+    if (nt) select(3);
     const uint64_t count = uint64_t(1) << (n - U::BITS - nh);
-    const int spread = !beyond_caches(n, sizeof(T) == 8) || hb[0] == 7 || hb[1] == 7;
+    const int spread = !nt || hb[0] == 7 || hb[1] == 7;
     auto go = [&](auto kern, int per_thread) {
         const unsigned per_group = 256 * per_thread;
         hipLaunchKernelGGL(kern, dim3((unsigned)((count + per_group - 1) / per_group)), dim3(256), 0, st,
                            (typename U::type*)psi, hb[0], hb[1], lomask, odd, spread, (T)cs, (T)sn, count);
     };
-    if (beyond_caches(n - nh, sizeof(T) == 8)) go(k_phase<T, NEG, true, 8>, 8);
-    else if (beyond_caches(n, sizeof(T) == 8)) go(k_phase<T, NEG, false, 8>, 8);
+    if (nt) go(k_phase<T, NEG, true, 8>, 8);
+    else if (beyond_caches(n, dbl)) go(k_phase<T, NEG, false, 1>, 1);
+    else if (hb[0] == 2) go(k_phase<T, NEG, false, 8>, 8);
     else go(k_phase<T, NEG, false, 2>, 2);
     return hipGetLastError();
 }
