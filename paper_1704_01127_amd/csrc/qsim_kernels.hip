@@ -963,7 +963,8 @@ __global__ __launch_bounds__(256, 1) void k_cluster_f32_split7(float2* __restric
     // work on one compact stretch per XCD (30 qubits, 23 target sets: 3.45 ms per
     // pass against 3.55 ms with a fixed stride, 3.74 ms without non-temporal
     // accesses as well); smaller states take a fixed stride (20 qubits: the
-    // counters cost 0.7 us).
+    // counters cost 0.7 us), and so do passes that take the sums, which come out
+    // the same bit for bit only if a wave's tiles are.
     const bool dealt = tickets != nullptr;
     const uint32_t mine = dealt ? blockIdx.x & 7 : 0u;
     const uint32_t nmine = (uint32_t)(dealt ? ntiles / 8 : ntiles);
